@@ -139,10 +139,18 @@ gm_status prepare(gm_batch* b, const TileConfig& cfg, hipStream_t s)
     b->launches.resize(b->sessions.size());
     b->items.clear();
     std::vector<double> cost;
+    // the sessions share one launch: automatic chunks follow the whole batch's size
+    double tile_fixations = 0.0;
+    for (const gm_session& ss : b->sessions)
+        tile_fixations += (double)((ss.n + 256 * cfg.spl - 1) / (256 * cfg.spl)) * (double)ss.fix.n;
     for (size_t i = 0; i < b->sessions.size(); ++i) {
         const gm_session& ss = b->sessions[i];
+        const int64_t tiles_i = std::max<int64_t>(1, (ss.n + 256 * cfg.spl - 1) / (256 * cfg.spl));
+        const int32_t chunk = cfg.chunk > 0
+                                  ? cfg.chunk
+                                  : auto_fix_per_chunk(tiles_i, ss.fix.n, tile_fixations, ss.flags & GM_OCC_MASK);
         gm_status st = density_prep(ss.scene, *b->work[i], ss.pos, ss.tri, ss.mesh, ss.n, &ss.fix, ss.theta_deg,
-                                    ss.flags & GM_OCC_MASK, cfg.spl, cfg.chunk, b->launches[i], s);
+                                    ss.flags & GM_OCC_MASK, cfg.spl, chunk, b->launches[i], s);
         if (st != GM_OK) return st;
         const DensityLaunch& a = b->launches[i];
         if (ss.n == 0 || ss.fix.n == 0) continue;

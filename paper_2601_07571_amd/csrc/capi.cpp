@@ -247,6 +247,34 @@ void density_sort(gm_scene* sc, DensityWork& w, const float* pos, const int32_t*
                    w.inv.as<int32_t>() + off, (int32_t)off, s);
 }
 
+int32_t auto_fix_per_chunk(int64_t tiles, int32_t F, double tile_fixations, uint32_t mode)
+{
+    // The cost of a (tile, chunk) item varies a lot (how many of its fixations see the tile),
+    // so a large grid holds many small items: at least ~512k of them and at most 1024
+    // fixations each, but chunks of no fewer than 128 fixations (512 without a visibility
+    // test, where an item costs little beyond its fixed part: its samples, the staging and
+    // the tile cone test of every fixation, the flush; the paper-shaped gate takes 2.43 ms at
+    // 128, 1.71 ms at 512, 1.74 ms at 1024).
+    // A launch of few tiles must cut its fixations finer to fill 256 CUs: the best chunk
+    // measured grows like the square root of the launch's (tile, fixation) pairs, which
+    // balances the items' fixed parts against the tail of the last ones.  Full occlusion,
+    // map time at chunks of 4 / 8 / 16 / 32 / 64 / 128 fixations: 25 tiles x 100 fixations
+    // 100 / 110 / 132 / 153 / 196 / 252 us; 47 x 2,501 1.17 / 1.11 / 1.17 / 1.22 / 1.43 /
+    // 1.97 ms; 196 x 1,000 1.32 / 1.25 / 1.34 / 1.68 / 2.05 / 3.25 ms; 1,173 x 3,000 6.8 /
+    // 5.2 / 4.2 / 3.7 / 3.7 / 4.4 ms; 1,563 x 12,000 38.9 / 29.7 / 24.2 / 21.1 / 19.7 / 19.4
+    // ms.  Without: 40 x 1,000 157 / 110 / 82 / 78 / 92 / 132 us; 391 x 3,000 2.17 / 1.48 /
+    // 0.93 / 0.56 / 0.33 / 0.27 ms (0.32 at 256, 0.46 at 512).
+    const bool occ = mode != GM_OCC_NONE;
+    const double root = std::sqrt(std::max(1.0, tile_fixations));
+    const int64_t min_chunk = std::min<int64_t>(occ ? 128 : 512, std::max<int64_t>(occ ? 4 : 16, (int64_t)(root / (occ ? 40.0 : 8.0))));
+    const int64_t max_chunks = std::max<int64_t>(1, (F + min_chunk - 1) / min_chunk);
+    const int64_t want = std::max<int64_t>((524288 + tiles - 1) / tiles, (F + 1023) / 1024);
+    // the grid is tiles x chunks: chunks <= 65535 (grid y) and tiles x chunks < 2^31
+    const int64_t cap = std::min<int64_t>(65535, std::max<int64_t>(1, INT32_MAX / tiles));
+    const int64_t chunks = std::min<int64_t>(std::min(max_chunks, cap), std::max<int64_t>(1, want));
+    return (int32_t)std::max<int64_t>(1, (F + chunks - 1) / chunks);
+}
+
 void density_args(const gm_scene* sc, const DensityWork& w, int64_t n, int32_t F, double sigma, uint32_t mode,
                   int spl, int32_t fix_per_chunk, DensityLaunch& a)
 {
@@ -266,23 +294,8 @@ void density_args(const gm_scene* sc, const DensityWork& w, int64_t n, int32_t F
     a.acc = w.acc.as<unsigned long long>();
     a.stats = w.stats.as<unsigned long long>();
     a.spl = spl;
-    if (fix_per_chunk <= 0) {
-        // The cost of a (tile, chunk) item varies a lot (how many of its fixations see
-        // the tile), so the grid holds many small items: at least ~512k of them and at
-        // most 1024 fixations each, but chunks of no fewer than 128 fixations.  Without
-        // a visibility test an item costs little beyond its fixed part (its samples,
-        // the staging and the tile cone test of every fixation, the flush), so chunks
-        // are at least 512 fixations long there (the paper-shaped gate: 2.43 ms at 128,
-        // 1.71 ms at 512, 1.74 ms at 1024).
-        const int64_t tiles = std::max<int64_t>(1, (n + 256 * spl - 1) / (256 * spl));
-        const int64_t min_chunk = mode == GM_OCC_NONE ? 512 : 128;
-        const int64_t max_chunks = std::max<int64_t>(1, (F + min_chunk - 1) / min_chunk);
-        const int64_t want = std::max<int64_t>((524288 + tiles - 1) / tiles, (F + 1023) / 1024);
-        // the grid is tiles x chunks: chunks <= 65535 (grid y) and tiles x chunks < 2^31
-        const int64_t cap = std::min<int64_t>(65535, std::max<int64_t>(1, INT32_MAX / tiles));
-        const int64_t chunks = std::min<int64_t>(std::min(max_chunks, cap), std::max<int64_t>(1, want));
-        fix_per_chunk = (int32_t)std::max<int64_t>(1, (F + chunks - 1) / chunks);
-    }
+    const int64_t tiles = std::max<int64_t>(1, (n + 256 * spl - 1) / (256 * spl));
+    if (fix_per_chunk <= 0) fix_per_chunk = auto_fix_per_chunk(tiles, F, (double)tiles * (double)F, mode);
     a.fix_per_chunk = fix_per_chunk;
     a.n_chunks = F > 0 ? (int32_t)((F + fix_per_chunk - 1) / fix_per_chunk) : 0;
     a.F_live = nullptr;

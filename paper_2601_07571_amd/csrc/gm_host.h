@@ -234,6 +234,9 @@ void density_sort(gm_scene* sc, DensityWork& w, const float* pos, const int32_t*
                   int64_t n, hipStream_t s, int64_t off = 0);
 void density_args(const gm_scene* sc, const DensityWork& w, int64_t n, int32_t F, double sigma, uint32_t mode,
                   int spl, int32_t fix_per_chunk, DensityLaunch& a);
+// fixations per work item for one launch (or one session of a batch) of `tiles` tiles and F
+// fixations, when the whole launch holds tile_fixations (tile, fixation) pairs
+int32_t auto_fix_per_chunk(int64_t tiles, int32_t F, double tile_fixations, uint32_t mode);
 // maximum and outputs
 gm_status density_finalize(DensityWork& w, int64_t n, float* density, float* density_norm, float* max_out,
                            hipStream_t s);
