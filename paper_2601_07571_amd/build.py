@@ -22,7 +22,7 @@ HOST_FLAGS = ["-O2", "-fPIC", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", os.p
 HIP_SOURCES = ["k_sampler.hip", "k_scan.hip", "k_density.hip", "k_field.hip", "capi.cpp", "field_api.cpp", "batch_api.cpp",
                "map_api.cpp", "export_api.cpp",
                "zbuffer_api.cpp", "noalloc_api.cpp"]
-HOST_SOURCES = ["bvh_build.cpp", "mesh_topology.cpp"]
+HOST_SOURCES = ["bvh_build.cpp", "mesh_topology.cpp", "solid_boxes.cpp"]
 # per-file flags: the field kernels keep matrix-core results in ordinary vector registers
 # (no copies out of the accumulation registers before the bias/ReLU/convert steps)
 EXTRA_FLAGS = {"k_field.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}

@@ -173,6 +173,11 @@ struct gm_scene {
     std::vector<uint8_t> closed, closed_topology;
     DevBuf closed_d, mbox_d;
     float bf_rmax = 0.0f;
+    // boxes inside the closed meshes and the tree over those whose flag is set (octant
+    // copies; solid_n nodes a copy, 0: none)
+    std::vector<gm::SolidBox> solid_boxes;
+    DevBuf solid;
+    int64_t solid_n = 0;
     bool any_closed() const
     {
         for (uint8_t c : closed)

@@ -74,6 +74,20 @@ struct HostBvh {
 void build_bvh(const float* V, const int32_t* I, const int32_t* tri_mesh, int64_t T, HostBvh& out,
                int leaf_max = kLeafMax);
 
+// Boxes inside closed meshes (solid_boxes.cpp, host): a segment that meets one on its way
+// to an eye outside its mesh's bounding box is occluded by that mesh.
+struct SolidBox {
+    float lo[3], hi[3];
+    int32_t mesh;
+};
+// at most max_boxes boxes of one closed mesh (vertices V, its own triangles I [T][3]);
+// scene_scale: largest coordinate magnitude of the scene
+void solid_boxes(const float* V, const int32_t* I, int64_t T, double scene_scale, int max_boxes, int32_t mesh,
+                 std::vector<SolidBox>& out);
+// a tree over the boxes of the meshes whose flag is set, in BvhNode form: child >= 0 a node,
+// count 1 and child ~m a box of mesh m; empty when there is none
+void build_solid_tree(const std::vector<SolidBox>& boxes, const std::vector<uint8_t>& closed, std::vector<BvhNode>& nodes);
+
 // ---------------------------------------------------------------------------
 // Launchers (defined in the .hip files).  All asynchronous on `s`.
 // ---------------------------------------------------------------------------
@@ -185,6 +199,10 @@ struct DensityLaunch {
     const float4* mbox = nullptr;
     const BvhTri* bf_tris = nullptr;
     float bf_L2max = 0.0f;
+    // The solid-box rule (static scenes; NULL: off): kNodeCopies octant copies of the tree
+    // over the boxes inside closed meshes, solid_stride nodes apart; uses mbox.
+    const BvhNode* solid = nullptr;
+    int64_t solid_stride = 0;
 };
 
 // Triangles of its own mesh listed per point for the back-face rule (more: the rule
@@ -248,6 +266,7 @@ struct BackfaceArgs {
     const float4* mbox = nullptr;
     float rmax = 0.0f;
     float l2max = 0.0f;
+    const BvhNode* solid = nullptr;  // plain copy of the solid-box tree (NULL: none)
 };
 void launch_pair_visibility(const float* pos, const int32_t* tri, const int32_t* mesh, const int32_t* tri_mesh,
                             const float* eye, const float* gaze, const int32_t* ps, const int32_t* pf, int64_t m,

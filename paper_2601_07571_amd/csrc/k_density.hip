@@ -160,9 +160,11 @@ struct Seg {
 
 constexpr float kTlo = (float)kEpsV;  // t of the segment's point end at which occluders start
 
+// The slab tests' inverse: the hardware reciprocal (one unit in the last place; the boxes'
+// padding is over ten times what that moves a slab), a tenth of the instructions of a division.
 __device__ __forceinline__ float safe_inv(float d)
 {
-    return fabsf(d) > 1e-30f ? 1.0f / d : copysignf(1e30f, d);
+    return fabsf(d) > 1e-30f ? __builtin_amdgcn_rcpf(d) : copysignf(1e30f, d);
 }
 
 __device__ __forceinline__ float pick(int k, float a, float b, float c) { return k == 0 ? a : (k == 1 ? b : c); }
@@ -482,6 +484,61 @@ __device__ void occluded_packet(const BvhNode* __restrict__ nodes, const BvhTri*
 }
 
 // ---------------------------------------------------------------------------
+// The solid-box rule.  A segment that meets a box inside a closed mesh M (no triangle of M
+// in it, M winding around it), where occluders count (t in [kTlo, 1]), on its way to an eye
+// outside M's bounding box crosses M beyond the box: it is occluded, by a triangle other
+// than the point's own (the box keeps its distance from every triangle).  The packet walks
+// the tree over those boxes (a few hundred at most: it stays in the scalar cache) as
+// occluded_packet walks the triangles'; a lane is done at its first box.  An occluded
+// packet then costs a few node visits instead of a descent to the triangles.
+// Returns the lanes of `live` that are occluded.
+// ---------------------------------------------------------------------------
+template <bool UNI>
+__device__ __forceinline__ uint64_t solid_packet(const BvhNode* __restrict__ nodes, const float4* __restrict__ mbox,
+                                                 int oct, const Seg& sg, float ex, float ey, float ez, int own_mesh,
+                                                 int mode, uint64_t live, TravCount& visits)
+{
+    const int lane = lane_id();
+    uint64_t hit = 0;
+    int stack = 0, sp = 0, node = 0;
+    while (live != 0) {
+        const BvhNode nd = load_node(nodes, node);
+        ++visits.nodes;
+        const uint64_t h0 = ballot(UNI ? box_hit_signed01(sg, nd.lo0, nd.hi0) : box_hit01(sg, nd.lo0, nd.hi0)) & live;
+        const uint64_t h1 = ballot(UNI ? box_hit_signed01(sg, nd.lo1, nd.hi1) : box_hit01(sg, nd.lo1, nd.hi1)) & live;
+        const bool swap = (oct >> ((nd.count0 >> kSplitAxisShift) & 3)) & 1;
+        int next = -1;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const bool first = (c == 0) != swap;
+            uint64_t h = (first ? h0 : h1) & live;
+            if (h == 0) continue;
+            const int child = first ? nd.child0 : nd.child1;
+            if (child < 0) {
+                const int m = ~child;
+                const float4 lo = mbox[2 * m], hi = mbox[2 * m + 1];
+                h &= ballot(ex < lo.x || ex > hi.x || ey < lo.y || ey > hi.y || ez < lo.z || ez > hi.z);
+                if (mode == 1) h &= ballot(own_mesh == m);
+                hit |= h;
+                live &= ~h;
+            } else if (next < 0) {
+                next = child;
+            } else {
+                stack = lane == sp ? child : stack;
+                ++sp;
+            }
+        }
+        if (next < 0) {
+            if (sp == 0) break;
+            --sp;
+            next = __builtin_amdgcn_readlane(stack, sp);
+        }
+        node = uniform(next);
+    }
+    return hit;
+}
+
+// ---------------------------------------------------------------------------
 // The back-face rule.  A point x on a triangle of a closed mesh M (a surface that bounds
 // a solid: winding number 0 outside, +1 across a triangle against its normal), seen from
 // an eye e outside M's bounding box with (e - x) . n < 0, has some triangle of M crossing
@@ -719,6 +776,8 @@ struct BfArgs {
     const int32_t* bcand;
     const float4* mbox;
     const BvhTri* tris;
+    const BvhNode* solid;
+    int64_t solid_stride;
     float l2max;
 };
 
@@ -1295,14 +1354,22 @@ __global__ void k_scatter(const float* __restrict__ pos, const int32_t* __restri
 // segments run between the points p[k] and the eye (ex, ey, ez), both in the frame of
 // the BVH whose octant node copies start at `nodes` (node_stride nodes apart) and
 // whose axis-permuted record copies start at `tris` (tri_stride records apart).
+// bf: the work item's rule buffers (bf->solid non-NULL: the solid-box rule first), or NULL.
 template <int SPL>
-__device__ __forceinline__ void packet_visibility(const BvhNode* __restrict__ nodes, int64_t node_stride,
+__device__ __forceinline__ void packet_visibility(const BfArgs* bf, const BvhNode* __restrict__ nodes, int64_t node_stride,
                                                   const BvhTri* __restrict__ tris, int64_t tri_stride, float ex,
                                                   float ey, float ez, float rx, float ry, float rz,
                                                   const float4 (&p)[SPL], const int (&otri)[SPL],
-                                                  const int (&omesh)[SPL], int mode, const bool (&need)[SPL],
+                                                  const int (&omesh)[SPL], int mode, const bool (&want)[SPL],
                                                   bool (&occl)[SPL], TravCount& n_visits)
 {
+    bool need[SPL], solid[SPL];
+#pragma unroll
+    for (int k = 0; k < SPL; ++k) {
+        need[k] = want[k];
+        solid[k] = false;
+    }
+    const BvhNode* sn = bf ? uniform_ptr(bf->solid) : nullptr;
     // Every lane shears along segment_axis: the gaze's dominant axis for every in-cone
     // segment at the cone angles in use.  When all of the packet's segments take it and
     // share their direction signs, the packet reads the record copy permuted into that
@@ -1345,6 +1412,16 @@ __device__ __forceinline__ void packet_visibility(const BvhNode* __restrict__ no
         }
         // eye-to-point octant (child order); the segments run the other way (node copy)
         const int oct = (nx_m != 0 ? 1 : 0) | (ny_m != 0 ? 2 : 0) | (nz_m != 0 ? 4 : 0);
+        if (sn) {
+            const BvhNode* so = sn + (oct ^ 7) * (int64_t)__builtin_amdgcn_readfirstlane((int)bf->solid_stride);
+            const float4* mb = uniform_ptr(bf->mbox);
+#pragma unroll
+            for (int k = 0; k < SPL; ++k) {
+                solid[k] = __builtin_amdgcn_inverse_ballot_w64(
+                    solid_packet<true>(so, mb, oct, sg[k], ex, ey, ez, omesh[k], mode, ballot(need[k]), n_visits));
+                need[k] = need[k] && !solid[k];
+            }
+        }
         occluded_packet<SPL, true>(nodes + (oct ^ 7) * node_stride, tris + gz * tri_stride, org, oct, sg, otri,
                                    omesh, mode, need, occl, n_visits);
     } else {
@@ -1358,9 +1435,20 @@ __device__ __forceinline__ void packet_visibility(const BvhNode* __restrict__ no
         // child order from one lane's octant (the order affects speed, not results)
         const int lead = __builtin_ctzll(nx_m | px_m);
         const int oct = (int)((nx_m >> lead) & 1) | (int)(((ny_m >> lead) & 1) << 1) | (int)(((nz_m >> lead) & 1) << 2);
+        if (sn) {
+            const float4* mb = uniform_ptr(bf->mbox);
+#pragma unroll
+            for (int k = 0; k < SPL; ++k) {
+                solid[k] = __builtin_amdgcn_inverse_ballot_w64(
+                    solid_packet<false>(sn, mb, oct, sg[k], ex, ey, ez, omesh[k], mode, ballot(need[k]), n_visits));
+                need[k] = need[k] && !solid[k];
+            }
+        }
         occluded_packet<SPL, false>(nodes, tris + 2 * tri_stride, org, oct, sg, otri, omesh, mode, need, occl,
                                     n_visits);
     }
+#pragma unroll
+    for (int k = 0; k < SPL; ++k) occl[k] = occl[k] || solid[k];
 }
 
 // The pair under the paper's approximation: inside the fixation's cropped frustum
@@ -1414,21 +1502,30 @@ __device__ __forceinline__ void density_item(const DensityLaunch& a, int64_t til
     __shared__ float4 s_co[3 * (FB + kGateGroup - 1)];
     __shared__ unsigned long long s_acc[kThreads * SPL];  // one entry per sample, owned by one lane
     __shared__ float s_rad;
+    __shared__ float4 s_o4;  // the tile origin, for the staging
     __shared__ uint32_t s_stats[kDensityStats];
     __shared__ uint32_t s_keep[kThreads / 64];  // fixations of the block kept by each staging wave
-    __shared__ BfArgs s_bf;                      // the back-face rule's buffers
+    __shared__ BfArgs s_bf;                      // the rules' buffers
+    // the gate's coordinates of each sample: kept in LDS where registers are tight (four fewer
+    // held across the walk)
+    constexpr bool kGateLds = SPL == 1 && OCC != 0;
+    __shared__ float4 s_pt[kGateLds ? kThreads : 1];
 
     const int lane = lane_id();
     const int wave = threadIdx.x >> 6;
-    const int64_t tile_base = tile * (int64_t)(kThreads * SPL);
-    const int64_t wave_base = tile_base + wave * (64 * SPL);
-    const int64_t n = a.n;
+    // sample indices in 32 bits (n < 2^31): one register each
+    const uint32_t tile_base = (uint32_t)tile * (uint32_t)(kThreads * SPL);
+    const uint32_t wave_base = tile_base + (uint32_t)wave * (64 * SPL);
+    const uint32_t n = (uint32_t)a.n;
 
     // tile origin: its first sample; radius: largest distance of a tile sample to it
     const float4 o4 = a.spos[tile_base];
-    if (threadIdx.x == 0) s_rad = 0.0f;
+    if (threadIdx.x == 0) {
+        s_rad = 0.0f;
+        s_o4 = o4;
+    }
     if (threadIdx.x < kDensityStats) s_stats[threadIdx.x] = 0u;
-    if (OCC != 0 && !ZB && threadIdx.x == 0) s_bf = BfArgs{a.bface, a.bcand, a.mbox, a.bf_tris, a.bf_L2max};
+    if (OCC != 0 && !ZB && threadIdx.x == 0) s_bf = BfArgs{a.bface, a.bcand, a.mbox, a.bf_tris, a.solid, a.solid_stride, a.bf_L2max};
     __syncthreads();
     uint32_t n_in = 0, n_vis = 0, n_trav = 0, n_bf = 0;  // wave-uniform counters
     TravCount n_visits;
@@ -1437,11 +1534,12 @@ __device__ __forceinline__ void density_item(const DensityLaunch& a, int64_t til
     float rad = 0.0f;
 #pragma unroll
     for (int k = 0; k < SPL; ++k) {
-        const int64_t i = wave_base + k * 64 + lane;
+        const uint32_t i = wave_base + (uint32_t)(k * 64 + lane);
         const float4 p = i < n ? a.spos[i] : o4;
         px[k] = p.x - o4.x; py[k] = p.y - o4.y; pz[k] = p.z - o4.z;
         pq[k] = __builtin_fmaf(px[k], px[k], __builtin_fmaf(py[k], py[k], pz[k] * pz[k]));
         rad = fmaxf(rad, pq[k]);
+        if (kGateLds) s_pt[threadIdx.x] = make_float4(px[k], py[k], pz[k], pq[k]);
         s_acc[wave * (64 * SPL) + k * 64 + lane] = 0ull;
     }
     atomicMax((unsigned int*)&s_rad, __float_as_uint(rad));
@@ -1469,7 +1567,8 @@ __device__ __forceinline__ void density_item(const DensityLaunch& a, int64_t til
         bool keep = false;
         if (threadIdx.x < nbf) {
             const FixRec fr = a.fix[fb + threadIdx.x];
-            const float ex = fr.ex - o4.x, ey = fr.ey - o4.y, ez = fr.ez - o4.z;
+            const float4 so = s_o4;
+            const float ex = fr.ex - so.x, ey = fr.ey - so.y, ez = fr.ez - so.z;
             const float e2 = __builtin_fmaf(ex, ex, __builtin_fmaf(ey, ey, ez * ez));
             const float c0 = -__builtin_fmaf(fr.rx, ex, __builtin_fmaf(fr.ry, ey, fr.rz * ez));
             if (fr.w > 0.0f) {  // zero weight: contributes nothing anywhere
@@ -1501,7 +1600,8 @@ __device__ __forceinline__ void density_item(const DensityLaunch& a, int64_t til
             // the record again (a cached reload: fewer registers held across the barrier)
             const int fidx = fb + threadIdx.x;
             const FixRec fr = a.fix[fidx];
-            const float ex = fr.ex - o4.x, ey = fr.ey - o4.y, ez = fr.ez - o4.z;
+            const float4 so = s_o4;
+            const float ex = fr.ex - so.x, ey = fr.ey - so.y, ez = fr.ez - so.z;
             const float e2 = __builtin_fmaf(ex, ex, __builtin_fmaf(ey, ey, ez * ez));
             const float k = fr.kappa;
             const float c0 = -__builtin_fmaf(fr.rx, ex, __builtin_fmaf(fr.ry, ey, fr.rz * ez));
@@ -1524,6 +1624,11 @@ __device__ __forceinline__ void density_item(const DensityLaunch& a, int64_t til
             // with no candidate costs one scalar test
             uint64_t gm[kGateGroup][SPL];
             uint64_t gany = 0;
+            if (kGateLds) {
+                asm volatile("" ::: "memory");  // read again for every fixation
+                const float4 q = s_pt[threadIdx.x];
+                px[0] = q.x; py[0] = q.y; pz[0] = q.z; pq[0] = q.w;
+            }
 #pragma unroll
             for (int h = 0; h < kGateGroup; ++h) {
                 const float4 ra = s_co[3 * (jg + h)];
@@ -1570,7 +1675,7 @@ __device__ __forceinline__ void density_item(const DensityLaunch& a, int64_t til
                 if (ZB) zc = reinterpret_cast<const ZCam*>(a.zcam)[f];
 #pragma unroll
                 for (int k = 0; k < SPL; ++k) {
-                    const int64_t i = wave_base + k * 64 + lane;
+                    const uint32_t i = wave_base + (uint32_t)(k * 64 + lane);
                     const bool c = __builtin_amdgcn_inverse_ballot_w64(cm[k]) && i < n;
                     g[k] = 0.0f;
                     p[k] = make_float4(fr.ex, fr.ey, fr.ez, __int_as_float(-1));
@@ -1597,7 +1702,7 @@ __device__ __forceinline__ void density_item(const DensityLaunch& a, int64_t til
                     any_need = false;
 #pragma unroll
                     for (int k = 0; k < SPL; ++k) {
-                        const int64_t i = wave_base + k * 64 + lane;
+                        const uint32_t i = wave_base + (uint32_t)(k * 64 + lane);
                         if (need[k] &&
                             backface_occluded(s_bf, a.smesh, i, p[k].x, p[k].y, p[k].z, fr.ex, fr.ey, fr.ez)) {
                             need[k] = false;
@@ -1611,14 +1716,14 @@ __device__ __forceinline__ void density_item(const DensityLaunch& a, int64_t til
                     int otri[SPL], omesh[SPL];
 #pragma unroll
                     for (int k = 0; k < SPL; ++k) {
-                        const int64_t i = wave_base + k * 64 + lane;
+                        const uint32_t i = wave_base + (uint32_t)(k * 64 + lane);
                         otri[k] = need[k] ? __float_as_int(p[k].w) : -1;
                         omesh[k] = need[k] ? a.smesh[i] : -1;
                     }
                     if (!INST) {
                         // the walk answers the lanes it tests; lanes the back-face rule settled keep it
                         bool o1[SPL];
-                        packet_visibility<SPL>(a.nodes, a.node_stride, a.tris, a.tri_stride, fr.ex, fr.ey, fr.ez, fr.rx,
+                        packet_visibility<SPL>(&s_bf, a.nodes, a.node_stride, a.tris, a.tri_stride, fr.ex, fr.ey, fr.ez, fr.rx,
                                                fr.ry, fr.rz, p, otri, omesh, a.occ_mode, need, o1, n_visits);
 #pragma unroll
                         for (int k = 0; k < SPL; ++k) occl[k] = occl[k] || o1[k];
@@ -1666,7 +1771,7 @@ __device__ __forceinline__ void density_item(const DensityLaunch& a, int64_t til
                                 }
                             }
                             bool o2[SPL];
-                            packet_visibility<SPL>(a.blas_nodes + b.node_base, b.node_count, a.blas_tris + b.tri_base,
+                            packet_visibility<SPL>(nullptr, a.blas_nodes + b.node_base, b.node_count, a.blas_tris + b.tri_base,
                                                    b.tri_count, fo.ex, fo.ey, fo.ez, fo.rx, fo.ry, fo.rz, q, otri, omesh,
                                                    2, rest, o2, n_visits);
 #pragma unroll
@@ -1686,7 +1791,7 @@ __device__ __forceinline__ void density_item(const DensityLaunch& a, int64_t til
     }
 #pragma unroll
     for (int k = 0; k < SPL; ++k) {
-        const int64_t i = wave_base + k * 64 + lane;
+        const uint32_t i = wave_base + (uint32_t)(k * 64 + lane);
         const unsigned long long v = s_acc[wave * (64 * SPL) + k * 64 + lane];
         if (i < n && v != 0ull) atomicAdd(&a.acc[i], v);
     }
@@ -1855,6 +1960,11 @@ __global__ void __launch_bounds__(64) k_pair_visibility(const float* __restrict_
             vis[i] = 0;
             return;
         }
+    }
+    if (bf.solid && mode != 0 &&
+        solid_packet<false>(bf.solid, bf.mbox, oct, sgs[0], ex, ey, ez, me, mode, 1ull, visits) != 0) {
+        if (lane == 0) vis[i] = 0;
+        return;
     }
     occluded_packet<1, false>(nodes, tris, org, oct, sgs, ot, om, mode, act, occ, visits);
     if (lane == 0) vis[i] = occ[0] ? 0 : 1;

@@ -386,6 +386,7 @@ gm_status gm_map_add_posed(gm_map* m, const gm_fixations* fix, const float* pose
             a.bcand += kBfCand * off;
         }
         if (m->mode != GM_OCC_NONE) {
+            a.solid = nullptr;  // the boxes are where the meshes were at rest
             a.blas = sc->blas_desc.as<BlasDesc>();
             a.blas_nodes = sc->blas_nodes.as<BvhNode>();
             a.blas_tris = sc->blas_tris.as<BvhTri>();
