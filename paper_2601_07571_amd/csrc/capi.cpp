@@ -327,6 +327,10 @@ void density_args(const gm_scene* sc, const DensityWork& w, int64_t n, int32_t F
         a.mbox = sc->mbox_d.as<float4>();
         a.bf_tris = sc->tris.as<BvhTri>() + 2 * sc->bvh.tris.size();
         a.bf_L2max = backface_l2max(sc);
+        if (w.horizon) {
+            a.hz = w.hz.as<float>();
+            a.hz_reach = sc->hz_reach;
+        }
     }
     if (mode != GM_OCC_NONE && sc->solid_n > 0) {
         a.solid = sc->solid.as<BvhNode>();
@@ -342,10 +346,11 @@ float backface_l2max(const gm_scene* sc)
     return (float)(lmax * lmax);
 }
 
-gm_status density_backface(gm_scene* sc, DensityWork& w, int64_t n, uint32_t mode, hipStream_t s, int64_t off)
+gm_status density_backface(gm_scene* sc, DensityWork& w, int64_t n, uint32_t mode, bool normals, hipStream_t s,
+                           int64_t off)
 {
     w.backface = false;
-    if (mode == GM_OCC_NONE || !sc->any_closed() || n <= 0) return GM_OK;
+    if (mode == GM_OCC_NONE || (!sc->any_closed() && !normals) || n <= 0) return GM_OK;
     GM_HIP(w.bface.ensure(16 * (size_t)(off + n)));
     GM_HIP(w.bcand.ensure(4 * (size_t)kBfCand * (size_t)(off + n)));
     launch_backface_prep(w.spos.as<float4>() + off, w.smesh.as<int32_t>() + off, n, sc->V.as<float>(),
@@ -354,6 +359,28 @@ gm_status density_backface(gm_scene* sc, DensityWork& w, int64_t n, uint32_t mod
                          w.bcand.as<int32_t>() + kBfCand * off, s);
     GM_HIP(hipGetLastError());
     w.backface = true;
+    return GM_OK;
+}
+
+bool horizon_pays(int64_t F, double sigma, uint32_t mode)
+{
+    // A point's walked pairs grow with F sigma^2 (its share of the cones), its horizon costs
+    // one walk of its neighbourhood.  Map time without / with: three objects and a terrain,
+    // 300,021 points, 2,500 fixations at 1 degree (F sigma^2 = 0.76) 3.68 / 3.97 ms; a sphere,
+    // 12,007 points, 2,501 at 1.2 degrees (1.1) 1.13 / 1.01; 2M points, 6,000 at 1 degree (1.8)
+    // 34.0 / 29.5; 25 spheres, 400,003 points, 12,000 (3.7) 15.4 / 14.3.
+    return mode != GM_OCC_NONE && (double)F * sigma * sigma >= 1.0;
+}
+
+gm_status density_horizon(gm_scene* sc, DensityWork& w, int64_t n, hipStream_t s)
+{
+    w.horizon = false;
+    if (!w.backface || n <= 0) return GM_OK;
+    GM_HIP(w.hz.ensure(4 * (size_t)n));
+    launch_horizon(w.spos.as<float4>(), w.bface.as<float4>(), n, sc->nodes.as<BvhNode>(),
+                   sc->tris.as<BvhTri>() + 2 * sc->bvh.tris.size(), sc->hz_reach, w.hz.as<float>(), s);
+    GM_HIP(hipGetLastError());
+    w.horizon = true;
     return GM_OK;
 }
 
@@ -369,7 +396,10 @@ gm_status density_prep(gm_scene* sc, DensityWork& w, const float* pos, const int
     launch_fix_prep(fix->eye, fix->gaze, fix->duration, F, sigma, kGateWiden, w.fix.as<FixRec>(), nullptr,
                     w.fx_shift.as<int32_t>(), s);
     density_sort(sc, w, pos, tri, mesh, n, s);
-    gm_status st = density_backface(sc, w, n, mode, s);
+    const bool horizon = horizon_pays(F, sigma, mode);
+    w.horizon = false;
+    gm_status st = density_backface(sc, w, n, mode, horizon, s);
+    if (st == GM_OK && horizon) st = density_horizon(sc, w, n, s);
     if (st != GM_OK) return st;
     density_args(sc, w, n, F, sigma, mode, spl, fix_per_chunk, a);
     GM_HIP(hipGetLastError());
@@ -470,6 +500,18 @@ gm_status gm_scene_create(const gm_mesh* meshes, int32_t n_meshes, gm_scene** ou
             mbox[(size_t)8 * m + c] = lo[c];
             mbox[(size_t)8 * m + 4 + c] = hi[c];
         }
+    }
+    {
+        double sum = 0.0;
+        for (const BvhTri& r : sc->bvh.tris) {
+            if (r.id < 0) continue;
+            for (int c = 0; c < 3; ++c)
+                sum += std::max(r.v0[c], std::max(r.v1[c], r.v2[c])) - std::min(r.v0[c], std::min(r.v1[c], r.v2[c]));
+        }
+        // four mean triangle extents: the map of 2M points x 6,000 fixations takes 33.1 / 31.6 /
+        // 31.3 ms at 2 / 4 / 8 (its horizons 1.4 / 2.1 / 3.3 of them), a sphere of 12,007 x 2,501
+        // 1.08 / 1.09 / 1.33
+        sc->hz_reach = (float)(4.0 * sum / (3.0 * (double)T));
     }
     sc->closed_topology = sc->closed;
     {
@@ -724,7 +766,7 @@ gm_status gm_debug_pair_visibility(gm_scene* sc, const float* pos, const int32_t
     gm_status st = check_device(sc);
     if (st != GM_OK) return st;
     BackfaceArgs bf;
-    if (sc->any_closed()) {
+    {
         bf.V = sc->V.as<float>();
         bf.I = sc->I.as<int32_t>();
         bf.closed = sc->closed_d.as<uint8_t>();

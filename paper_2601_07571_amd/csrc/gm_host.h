@@ -130,6 +130,8 @@ struct DensityWork {
     DevBuf fix, fx_shift, key, hist, cursor, scan_tmp, spos, smesh, inv, acc, max_acc, stats, zcam, zbuf;
     DevBuf bface, bcand;  // back-face rule data of the sorted points (see DensityLaunch::bface)
     bool backface = false;  // bface / bcand hold the current points' data
+    DevBuf hz;              // their horizons (see DensityLaunch::hz)
+    bool horizon = false;   // hz holds the current points' data
     int bits = 1;
     int64_t buckets = 8;
 };
@@ -173,6 +175,7 @@ struct gm_scene {
     std::vector<uint8_t> closed, closed_topology;
     DevBuf closed_d, mbox_d;
     float bf_rmax = 0.0f;
+    float hz_reach = 0.0f;  // distance from a point within which its horizon holds every triangle
     // boxes inside the closed meshes and the tree over those whose flag is set (octant
     // copies; solid_n nodes a copy, 0: none)
     std::vector<gm::SolidBox> solid_boxes;
@@ -229,7 +232,13 @@ gm_status density_prep(gm_scene* sc, DensityWork& w, const float* pos, const int
                        int32_t fix_per_chunk, DensityLaunch& a, hipStream_t s);
 // the back-face rule's data of the n sorted points from entry off of w (static scenes with
 // a closed mesh and occlusion on; otherwise it marks the rule off)
-gm_status density_backface(gm_scene* sc, DensityWork& w, int64_t n, uint32_t mode, hipStream_t s, int64_t off = 0);
+// (normals: also without a closed mesh, for the horizon rule)
+gm_status density_backface(gm_scene* sc, DensityWork& w, int64_t n, uint32_t mode, bool normals, hipStream_t s,
+                           int64_t off = 0);
+// whether the points' horizons pay for themselves over F fixations
+bool horizon_pays(int64_t F, double sigma, uint32_t mode);
+// the horizons of the n sorted points of w, whose normals density_backface has written
+gm_status density_horizon(gm_scene* sc, DensityWork& w, int64_t n, hipStream_t s);
 // squared length of the longest segment the rule takes (see DensityLaunch::bf_L2max)
 float backface_l2max(const gm_scene* sc);
 // the two halves of density_prep's point side: zeroed accumulators and the spatial sort

@@ -190,8 +190,9 @@ struct DensityLaunch {
     // The back-face rule (static scenes; NULL bface: off).  Per sorted point: the unit
     // normal of its own triangle times the point's distance to that triangle's edges
     // and, in w, the number of triangles of its mesh within
-    // bf_rmax of it (as int bits; -1: the rule does not apply to the point), whose
-    // record indices (plain x, y, z copy) are bcand[kBfCand * i + j].  mbox: per mesh the
+    // bf_rmax of it (as int bits, low byte; -1: the rule does not apply to the point), whose
+    // record indices (plain x, y, z copy) are bcand[kBfCand * i + j], and above it 16 bits
+    // of the steepest slope below the plane that they reach (as sin^2; all ones: any).  mbox: per mesh the
     // bounding box, lo then hi (2 float4).  A segment longer than sqrt(bf_L2max) is left
     // to the traversal.
     const float4* bface = nullptr;
@@ -199,6 +200,11 @@ struct DensityLaunch {
     const float4* mbox = nullptr;
     const BvhTri* bf_tris = nullptr;
     float bf_L2max = 0.0f;
+    // The horizon rule (static scenes; NULL: off): per sorted point sin^2 of the
+    // elevation over its triangle's plane above which a segment meets no triangle within
+    // hz_reach of it.
+    const float* hz = nullptr;
+    float hz_reach = 0.0f;
     // The solid-box rule (static scenes; NULL: off): kNodeCopies octant copies of the tree
     // over the boxes inside closed meshes, solid_stride nodes apart; uses mbox.
     const BvhNode* solid = nullptr;
@@ -387,5 +393,9 @@ bool mesh_is_closed(const float* V, int64_t nv, const int32_t* I, int64_t T);
 void launch_backface_prep(const float4* spos, const int32_t* smesh, int64_t n, const float* V, const int32_t* I,
                           const uint8_t* closed, const BvhNode* nodes, const BvhTri* tris, float rmax,
                           float4* bface, int32_t* bcand, hipStream_t s);
+// Per sorted point the horizon of the triangles within `reach` of it above its own
+// triangle's plane (see DensityLaunch::hz), from the normals in bface.
+void launch_horizon(const float4* spos, const float4* bface, int64_t n, const BvhNode* nodes, const BvhTri* tris,
+                    float reach, float* hz, hipStream_t s);
 
 }  // namespace gm

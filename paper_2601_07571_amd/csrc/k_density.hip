@@ -155,6 +155,7 @@ struct Seg {
     float qx, qy, qz;  // -x / direction
     float sx, sy;      // watertight shear: d[kx] / d[kz], d[ky] / d[kz]
     float tz;          // d[kz]
+    float t0;          // the walk's box tests begin here (at least kTlo)
     int kx, ky, kz;    // axis order of the shear
 };
 
@@ -223,6 +224,7 @@ __device__ __forceinline__ Seg make_seg(float xx, float xy, float xz, float ex, 
     s.sx = pick(kx, dx, dy, dz) / dkz;
     s.sy = pick(ky, dx, dy, dz) / dkz;
     s.tz = dkz;
+    s.t0 = kTlo;
     return s;
 }
 
@@ -268,7 +270,7 @@ __device__ __forceinline__ bool box_hit_signed01(const Seg& s, const float* near
     const float nx = fma01(near[0], s.ix, s.qx), fx = fma01(far[0], s.ix, s.qx);
     const float ny = fma01(near[1], s.iy, s.qy), fy = fma01(far[1], s.iy, s.qy);
     const float nz = fma01(near[2], s.iz, s.qz), fz = fma01(far[2], s.iz, s.qz);
-    const float tn = fmaxf(fmaxf(fmaxf(nx, ny), nz), kTlo);
+    const float tn = fmaxf(fmaxf(fmaxf(nx, ny), nz), s.t0);
     const float tf = fminf(fminf(fx, fy), fz);
     return tn < tf;
 }
@@ -278,7 +280,7 @@ __device__ __forceinline__ bool box_hit01(const Seg& s, const float* lo, const f
     const float t0x = fma01(lo[0], s.ix, s.qx), t1x = fma01(hi[0], s.ix, s.qx);
     const float t0y = fma01(lo[1], s.iy, s.qy), t1y = fma01(hi[1], s.iy, s.qy);
     const float t0z = fma01(lo[2], s.iz, s.qz), t1z = fma01(hi[2], s.iz, s.qz);
-    const float tn = fmaxf(fmaxf(fmaxf(fminf(t0x, t1x), fminf(t0y, t1y)), fminf(t0z, t1z)), kTlo);
+    const float tn = fmaxf(fmaxf(fmaxf(fminf(t0x, t1x), fminf(t0y, t1y)), fminf(t0z, t1z)), s.t0);
     const float tf = fminf(fminf(fmaxf(t0x, t1x), fmaxf(t0y, t1y)), fmaxf(t0z, t1z));
     return tn < tf;
 }
@@ -539,6 +541,115 @@ __device__ __forceinline__ uint64_t solid_packet(const BvhNode* __restrict__ nod
 }
 
 // ---------------------------------------------------------------------------
+// Slopes of triangles seen from a point x on a surface with unit normal n: a direction's
+// slope is its component along n over the one across it, the same all along a segment from
+// x, so a segment steeper than a bound H of a triangle's slopes does not meet that triangle.
+// Bounds are rounded up (relative 2e-6 of the distances for FP32, slopes by 1e-4 and 1e-3),
+// far more than the error of the segment test.
+// ---------------------------------------------------------------------------
+constexpr float kHzFloor = 0.08f;   // slopes below this are not told apart (5 degrees)
+constexpr float kHzCap = 4.0f;      // a point whose horizon is this high is left to the walk
+constexpr int kHzVisits = 3000;     // node visits of one wave's walk (more: the rule is off for its points)
+constexpr float kHzBelow = 0.02f;   // the same for the neighbours below the plane (back-face rule)
+constexpr float kHzNever = 2.0f;
+
+struct HzPoint {
+    float x, y, z, nx, ny, nz;     // the point and the unit normal
+    float ux, uy, uz, vx, vy, vz;  // an orthonormal pair across it
+    float H;
+};
+
+__device__ __forceinline__ HzPoint hz_point(float px, float py, float pz, float nx, float ny, float nz, float h)
+{
+    HzPoint P;
+    P.x = px; P.y = py; P.z = pz;
+    P.nx = nx; P.ny = ny; P.nz = nz;
+    // an orthonormal pair: the axis after the dominant one, less its part along n
+    const int kz = dominant_axis(nx, ny, nz);
+    const float ox = kz == 2 ? 1.0f : 0.0f, oy = kz == 0 ? 1.0f : 0.0f, oz = kz == 1 ? 1.0f : 0.0f;
+    const float d = __builtin_fmaf(ox, nx, __builtin_fmaf(oy, ny, oz * nz));
+    const float wx = ox - d * nx, wy = oy - d * ny, wz = oz - d * nz;
+    const float wi = rsqrtf(fmaxf(__builtin_fmaf(wx, wx, __builtin_fmaf(wy, wy, wz * wz)), 1e-30f));
+    P.ux = wx * wi; P.uy = wy * wi; P.uz = wz * wi;
+    P.vx = ny * P.uz - nz * P.uy; P.vy = nz * P.ux - nx * P.uz; P.vz = nx * P.uy - ny * P.ux;
+    P.H = h;
+    return P;
+}
+
+// A triangle: two bounds of its slopes, the lower taken.  Its highest point over its least
+// distance from the normal's line (the largest of the origin's outside distances to its
+// projected edges); and its plane's: on a plane of slope g that passes the normal's line at
+// height h0, slopes stay below g + max(h0, 0) / r.  The second keeps a concave neighbour,
+// which begins right beside x and rises away from it, at its own inclination.
+__device__ __forceinline__ void hz_tri(HzPoint& P, const BvhTri& t)
+{
+    const float ax = t.v0[0] - P.x, ay = t.v0[1] - P.y, az = t.v0[2] - P.z;
+    const float bx = t.v1[0] - P.x, by = t.v1[1] - P.y, bz = t.v1[2] - P.z;
+    const float cx = t.v2[0] - P.x, cy = t.v2[1] - P.y, cz = t.v2[2] - P.z;
+    const float a2 = __builtin_fmaf(ax, ax, __builtin_fmaf(ay, ay, az * az));
+    const float b2 = __builtin_fmaf(bx, bx, __builtin_fmaf(by, by, bz * bz));
+    const float c2 = __builtin_fmaf(cx, cx, __builtin_fmaf(cy, cy, cz * cz));
+    const float d2 = fmaxf(fmaxf(a2, b2), c2);
+    const float dm = 2e-6f * sqrtf(d2);
+    const float ha = __builtin_fmaf(P.nx, ax, __builtin_fmaf(P.ny, ay, P.nz * az));
+    const float hb = __builtin_fmaf(P.nx, bx, __builtin_fmaf(P.ny, by, P.nz * bz));
+    const float hc = __builtin_fmaf(P.nx, cx, __builtin_fmaf(P.ny, cy, P.nz * cz));
+    const float top = fmaxf(fmaxf(ha, hb), hc) + dm;
+    if (!(top > 0.0f)) return;
+    const float au = __builtin_fmaf(P.ux, ax, __builtin_fmaf(P.uy, ay, P.uz * az));
+    const float av = __builtin_fmaf(P.vx, ax, __builtin_fmaf(P.vy, ay, P.vz * az));
+    const float bu = __builtin_fmaf(P.ux, bx, __builtin_fmaf(P.uy, by, P.uz * bz));
+    const float bv = __builtin_fmaf(P.vx, bx, __builtin_fmaf(P.vy, by, P.vz * bz));
+    const float cu = __builtin_fmaf(P.ux, cx, __builtin_fmaf(P.uy, cy, P.uz * cz));
+    const float cv = __builtin_fmaf(P.vx, cx, __builtin_fmaf(P.vy, cy, P.vz * cz));
+    const float kab = diff_of_products(au, bv, av, bu), kbc = diff_of_products(bu, cv, bv, cu),
+                kca = diff_of_products(cu, av, cv, au);
+    const float sg = kab + kbc + kca < 0.0f ? -1.0f : 1.0f;
+    const float lab = __builtin_fmaf(bu - au, bu - au, (bv - av) * (bv - av));
+    const float lbc = __builtin_fmaf(cu - bu, cu - bu, (cv - bv) * (cv - bv));
+    const float lca = __builtin_fmaf(au - cu, au - cu, (av - cv) * (av - cv));
+    // an edge seen end-on (no length across the normal) gives no distance
+    const float oab = lab > 0.0f ? -sg * kab * rsqrtf(lab) : -1.0f;
+    const float obc = lbc > 0.0f ? -sg * kbc * rsqrtf(lbc) : -1.0f;
+    const float oca = lca > 0.0f ? -sg * kca * rsqrtf(lca) : -1.0f;
+    const float rl = fmaxf(fmaxf(oab, obc), oca) - dm;
+    const float ri = rl > 0.0f ? __builtin_amdgcn_rcpf(rl) : INFINITY;
+    float s = top * ri;
+    if (s > P.H) {
+        const float px = bx - ax, py = by - ay, pz = bz - az, qx = cx - ax, qy = cy - ay, qz = cz - az;
+        const float mx = diff_of_products(py, qz, pz, qy), my = diff_of_products(pz, qx, px, qz),
+                    mz = diff_of_products(px, qy, py, qx);
+        const float m2 = __builtin_fmaf(mx, mx, __builtin_fmaf(my, my, mz * mz));
+        const float p2 = __builtin_fmaf(px, px, __builtin_fmaf(py, py, pz * pz));
+        const float q2 = __builtin_fmaf(qx, qx, __builtin_fmaf(qy, qy, qz * qz));
+        const float mn = __builtin_fmaf(mx, P.nx, __builtin_fmaf(my, P.ny, mz * P.nz));
+        // the plane's bound, for a triangle not small against its distance (a small one is well
+        // bounded above) whose normal is well determined: tilted by at most 3e-5 from rounding
+        if (m2 > 1e-3f * p2 * q2 && mn * mn > 0.2f * m2 && 64.0f * fminf(p2, q2) > d2) {
+            const float g = sqrtf(fmaxf(m2 - mn * mn, 0.0f)) / fabsf(mn);
+            const float h0 = __builtin_fmaf(mx, ax, __builtin_fmaf(my, ay, mz * az)) / mn + 25.0f * dm;
+            s = fminf(s, h0 <= 0.0f ? g : __builtin_fmaf(h0, ri, g));
+        }
+        P.H = fmaxf(P.H, __builtin_fmaf(s, 1.0002f, 1e-3f));
+    }
+}
+
+// sin^2 of the elevation of slope H, rounded up; kHzNever at or above the cap
+__device__ __forceinline__ float hz_sin2(float H)
+{
+    return H < kHzCap ? H * H / __builtin_fmaf(H, H, 1.0f) * 1.00001f : kHzNever;
+}
+
+// Is the direction u, of squared length l2, steeper over the plane of normal n (of any
+// positive length) than a horizon of sin^2 h?
+__device__ __forceinline__ bool steeper(float h, float nx, float ny, float nz, float ux, float uy, float uz, float l2)
+{
+    const float dn = __builtin_fmaf(nx, ux, __builtin_fmaf(ny, uy, nz * uz));
+    const float n2 = __builtin_fmaf(nx, nx, __builtin_fmaf(ny, ny, nz * nz));
+    return dn > 0.0f && dn * dn > h * (l2 * n2);
+}
+
+// ---------------------------------------------------------------------------
 // The back-face rule.  A point x on a triangle of a closed mesh M (a surface that bounds
 // a solid: winding number 0 outside, +1 across a triangle against its normal), seen from
 // an eye e outside M's bounding box with (e - x) . n < 0, has some triangle of M crossing
@@ -566,17 +677,17 @@ __device__ __forceinline__ float box_dist2(float x, float y, float z, const floa
 // it, by one packet walk of the scene BVH per wave (wave-uniform node, the lane's sphere
 // against both child boxes; squared distances against rmax^2 widened by 1e-3).  cnt =
 // -1: the rule does not apply (no closed mesh, degenerate triangle, more than kBfCand
-// neighbours).  Every lane of the wave must call it.
+// neighbours).  The normal is given for points of open meshes too (the horizon rule).  Every lane of the wave must call it.
 __device__ __forceinline__ void backface_point(float px, float py, float pz, int t, int m, bool on,
                                                const float* __restrict__ V, const int32_t* __restrict__ I,
                                                const uint8_t* __restrict__ closed,
                                                const BvhNode* __restrict__ nodes, const BvhTri* __restrict__ tris,
-                                               float rmax, float& nx, float& ny, float& nz, int& cnt,
+                                               float rmax, float& nx, float& ny, float& nz, float& below, int& cnt,
                                                int (&cand)[kBfCand])
 {
     const int lane = lane_id();
     nx = ny = nz = 0.0f;
-    on = on && t >= 0 && m >= 0 && closed[m] != 0;
+    on = on && t >= 0;
     if (on) {
         const int i0 = I[3 * t], i1 = I[3 * t + 1], i2 = I[3 * t + 2];
         const float ax = V[3 * i0], ay = V[3 * i0 + 1], az = V[3 * i0 + 2];
@@ -608,6 +719,7 @@ __device__ __forceinline__ void backface_point(float px, float py, float pz, int
         const float sc = on ? inv * D : 0.0f;
         nx *= sc; ny *= sc; nz *= sc;
     }
+    on = on && m >= 0 && closed[m] != 0;  // the neighbours: closed meshes only
     const float r2 = rmax * rmax * 1.001f;
     cnt = 0;
 #pragma unroll
@@ -659,6 +771,26 @@ __device__ __forceinline__ void backface_point(float px, float py, float pz, int
         node = uniform(next);
     }
     if (!on || cnt > kBfCand) cnt = -1;
+    // the neighbours' slopes below the plane
+    const float ni = rsqrtf(fmaxf(__builtin_fmaf(nx, nx, __builtin_fmaf(ny, ny, nz * nz)), 1e-36f));
+    HzPoint P = hz_point(px, py, pz, -nx * ni, -ny * ni, -nz * ni, kHzBelow);
+#pragma unroll
+    for (int j = 0; j < kBfCand; ++j)
+        if (j < cnt) hz_tri(P, load_tri_v(tris, cand[j]));
+    below = hz_sin2(P.H);
+}
+
+// cnt (-1, or 0 .. kBfCand) and the neighbours' sin^2 below the plane (16 bits, rounded up;
+// all ones: none), as kept in bface.w
+__device__ __forceinline__ int pack_neighbours(int cnt, float below)
+{
+    return cnt < 0 ? -1 : (cnt | ((int)fminf(ceilf(below * 65534.0f), 65535.0f) << 8));
+}
+
+__device__ __forceinline__ float unpack_below(int w)
+{
+    const int q = (w >> 8) & 0xffff;
+    return q == 65535 ? kHzNever : (float)q * (1.0f / 65534.0f);
 }
 
 // 2^lg consecutive (sorted) points per wave, the other lanes idle.  A wave's radius queries
@@ -692,12 +824,12 @@ __global__ void __launch_bounds__(256) k_backface_prep(const float4* __restrict_
         p = spos[i];
         m = smesh[i];
     }
-    float nx, ny, nz;
+    float nx, ny, nz, below;
     int cnt, cand[kBfCand];
-    backface_point(p.x, p.y, p.z, __float_as_int(p.w), m, i < n, V, I, closed, nodes, tris, rmax, nx, ny, nz, cnt,
+    backface_point(p.x, p.y, p.z, __float_as_int(p.w), m, i < n, V, I, closed, nodes, tris, rmax, nx, ny, nz, below, cnt,
                    cand);
     if (i < n) {
-        bface[i] = make_float4(nx, ny, nz, __int_as_float(cnt));
+        bface[i] = make_float4(nx, ny, nz, __int_as_float(pack_neighbours(cnt, below)));
 #pragma unroll
         for (int j = 0; j < kBfCand; ++j)
             if (j < cnt) bcand[kBfCand * i + j] = cand[j];
@@ -751,7 +883,7 @@ __device__ __forceinline__ bool stretch_may_cross(float xx, float xy, float xz, 
 // inward normal), inside the triangle while c D >= 4 eta, which the rule requires: so
 // the segment does enter the solid through the triangle (or starts inside it).
 template <class Cand>
-__device__ __forceinline__ bool backface_rule(float nx, float ny, float nz, int cnt, const Cand& cand, float xx,
+__device__ __forceinline__ bool backface_rule(float nx, float ny, float nz, int cnt, float below, const Cand& cand, float xx,
                                               float xy, float xz, float ex, float ey, float ez, float4 lo, float4 hi,
                                               float l2max, const BvhTri* __restrict__ tris)
 {
@@ -762,6 +894,9 @@ __device__ __forceinline__ bool backface_rule(float nx, float ny, float nz, int 
     const float eta = 5.9604645e-8f * (fabsf(xx) + fabsf(xy) + fabsf(xz));
     if (!(dn < 0.0f && dn * dn >= 16.0f * eta * eta * l2 && l2 <= l2max)) return false;
     if (!(ex < lo.x || ex > hi.x || ey < lo.y || ey > hi.y || ez < lo.z || ez > hi.z)) return false;
+    // steeper below the plane than every neighbour: none can be crossed (all but grazing
+    // pairs end here, without the gathers and tests below: 28.0 -> 27.0 ms on the 2M map)
+    if (dn * dn > below * (l2 * __builtin_fmaf(nx, nx, __builtin_fmaf(ny, ny, nz * nz)))) return true;
     for (int j = 0; j < cnt; ++j)
         if (stretch_may_cross(xx, xy, xz, ux, uy, uz, load_tri_v(tris, cand(j)))) return false;
     return true;
@@ -776,6 +911,8 @@ struct BfArgs {
     const int32_t* bcand;
     const float4* mbox;
     const BvhTri* tris;
+    const float* hz;
+    float hz_reach;
     const BvhNode* solid;
     int64_t solid_stride;
     float l2max;
@@ -790,17 +927,142 @@ __device__ __forceinline__ T* uniform_ptr(T* p)
     return (T*)(((uint64_t)hi << 32) | lo);
 }
 
-__device__ __forceinline__ bool backface_occluded(const BfArgs& s_bf, const int32_t* smesh, int64_t i, float xx,
-                                                  float xy, float xz, float ex, float ey, float ez)
+// ---------------------------------------------------------------------------
+// The horizon rule.  Seen from a point x on a triangle with unit normal n, everything that
+// can hide x in a direction of the normal's side has at least that direction's slope: the
+// component along n over the one across it, the same all along a segment from x.  H bounds
+// the slopes of all scene triangles (but x's own) that come within `reach` of x, so a segment
+// steeper than H meets none of them, and its walk may begin at distance `reach`: the leaves
+// around its point, which every packet of a surface otherwise descends to, fall away, and
+// what is left is the upper tree and whatever else stands in the way.
+//
+// H comes from one walk of the scene BVH per point (a packet of the wave's points, as the
+// back-face lists): a child box, or a triangle, that reaches above the plane through x bounds
+// the slopes of its contents by its highest point over its least distance from the normal's
+// line; a box within reach is opened while that exceeds H.  All bounds are rounded up
+// (relative 2e-6 of the distances for FP32, slopes by 1e-4 and 1e-3), far more than the
+// error of the segment test.  Stored is sin^2 of the elevation, H^2 / (1 + H^2).
+// VALU bound (43 instructions a box, about 85 a triangle, 64 points at a time when they are
+// dense); 2M points: 2.1 ms, and the density kernel 33.5 -> 26.5 ms at 6,000 fixations.  Slopes
+// kept per azimuth (eight sectors) and horizons of the whole scene settled little more for
+// twice and ten times the cost.
+// ---------------------------------------------------------------------------
+// Does the lane have to open a child box (else its contents are beyond reach, below the
+// plane or below H)?  s: its slope bound.
+__device__ __forceinline__ bool hz_box(const HzPoint& P, const float* lo, const float* hi, float reach2, float& s)
 {
-    const float4* bface = uniform_ptr(s_bf.bface);
-    const float4 bf = bface[i];
+    const float lx = lo[0] - P.x, ly = lo[1] - P.y, lz = lo[2] - P.z;
+    const float hx = hi[0] - P.x, hy = hi[1] - P.y, hz = hi[2] - P.z;
+    const float gx = fmaxf(fmaxf(lx, -hx), 0.0f), gy = fmaxf(fmaxf(ly, -hy), 0.0f), gz = fmaxf(fmaxf(lz, -hz), 0.0f);
+    const float cx = lx + hx, cy = ly + hy, cz = lz + hz;  // twice the centre, and the extent
+    const float ex = hx - lx, ey = hy - ly, ez = hz - lz;
+    const float c2 = __builtin_fmaf(cx, cx, __builtin_fmaf(cy, cy, cz * cz));
+    const float rho = sqrtf(__builtin_fmaf(ex, ex, __builtin_fmaf(ey, ey, ez * ez)));
+    const float hc = __builtin_fmaf(P.nx, cx, __builtin_fmaf(P.ny, cy, P.nz * cz));
+    const float dm = 2e-6f * (sqrtf(c2) + rho);
+    const float top = hc + __builtin_fmaf(fabsf(P.nx), ex, __builtin_fmaf(fabsf(P.ny), ey, fabsf(P.nz) * ez)) + dm;
+    const float rl = sqrtf(fmaxf(c2 - hc * hc, 0.0f)) - rho - dm;
+    s = rl > 0.0f ? __builtin_fmaf(top * __builtin_amdgcn_rcpf(rl), 1.0002f, 1e-3f) : (top > 0.0f ? INFINITY : 0.0f);
+    return __builtin_fmaf(gx, gx, __builtin_fmaf(gy, gy, gz * gz)) <= reach2 && s > P.H;
+}
+
+// The horizon of one point per lane (own triangle t, normal n of any positive length; on:
+// the rule may be used) as sin^2 of its elevation, kHzNever: none.  Every lane of the wave
+// must call it.
+__device__ __forceinline__ float horizon_point(float px, float py, float pz, float nx, float ny, float nz, int t, bool on,
+                                               float reach, const BvhNode* __restrict__ nodes,
+                                               const BvhTri* __restrict__ tris)
+{
+    const int lane = lane_id();
+    const float reach2 = reach * reach * 1.001f;
+    const float n2 = __builtin_fmaf(nx, nx, __builtin_fmaf(ny, ny, nz * nz));
+    on = on && t >= 0 && n2 >= 1e-30f;
+    const float inv = on ? rsqrtf(n2) : 0.0f;
+    HzPoint P = hz_point(px, py, pz, nx * inv, ny * inv, nz * inv, kHzFloor);
+    uint64_t live = ballot(on);
+    int stack = 0, sp = 0, node = 0, visits = 0;
+    bool whole = true;
+    while (live != 0) {
+        if (++visits > kHzVisits) {
+            whole = false;
+            break;
+        }
+        const BvhNode nd = load_node(nodes, node);
+        float s0, s1;
+        const uint64_t m0 = ballot(hz_box(P, nd.lo0, nd.hi0, reach2, s0)) & live;
+        const uint64_t m1 = ballot(hz_box(P, nd.lo1, nd.hi1, reach2, s1)) & live;
+        int next = -1;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const uint64_t m = c == 0 ? m0 : m1;
+            if (m == 0) continue;
+            const int child = c == 0 ? nd.child0 : nd.child1;
+            const int count = (c == 0 ? nd.count0 : nd.count1) & kCountMask;
+            if (child < 0) {
+                const bool test = __builtin_amdgcn_inverse_ballot_w64(m);
+                for (int k = 0; k < count; ++k) {
+                    const BvhTri tr = load_tri(tris, ~child + k);
+                    if (test && tr.id != t) hz_tri(P, tr);
+                }
+            } else if (next < 0) {
+                next = child;
+            } else {
+                stack = lane == sp ? child : stack;
+                ++sp;
+            }
+        }
+        if (next < 0) {
+            live &= ballot(P.H < kHzCap);  // the others have nothing left to find
+            if (sp == 0) break;
+            --sp;
+            next = __builtin_amdgcn_readlane(stack, sp);
+        }
+        node = uniform(next);
+    }
+    return on && whole ? hz_sin2(P.H) : kHzNever;
+}
+
+__global__ void __launch_bounds__(256) k_horizon(const float4* __restrict__ spos, const float4* __restrict__ bface,
+                                                 int64_t n, const BvhNode* __restrict__ nodes,
+                                                 const BvhTri* __restrict__ tris, float reach, int lg,
+                                                 float* __restrict__ hz)
+{
+    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int lane = (int)(g & 63);
+    const int64_t i = lane < (1 << lg) ? ((g >> 6) << lg) + lane : n;  // n: an idle lane
+    float4 p = make_float4(0.0f, 0.0f, 0.0f, __int_as_float(-1)), b = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (i < n) {
+        p = spos[i];
+        b = bface[i];
+    }
+    const float h = horizon_point(p.x, p.y, p.z, b.x, b.y, b.z, __float_as_int(p.w), i < n, reach, nodes, tris);
+    if (i < n) hz[i] = h;
+}
+
+// What the rules say of point i (sorted order) and eye e: true when the pair is occluded by
+// the point's own closed mesh; else t0 is where the walk of its segment may begin (beyond the
+// part that the horizon clears, else kTlo; 1: all of it is clear).
+__device__ __forceinline__ bool settled_by_rule(const BfArgs& s_bf, const int32_t* smesh, uint32_t i, float xx, float xy,
+                                                float xz, float ex, float ey, float ez, float& t0)
+{
+    t0 = kTlo;
+    const float4 bf = uniform_ptr(s_bf.bface)[i];
+    const float* hz = uniform_ptr(s_bf.hz);
+    if (hz) {
+        const float ux = ex - xx, uy = ey - xy, uz = ez - xz;
+        const float l2 = __builtin_fmaf(ux, ux, __builtin_fmaf(uy, uy, uz * uz));
+        if (steeper(hz[i], bf.x, bf.y, bf.z, ux, uy, uz, l2)) {
+            const float reach = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(s_bf.hz_reach)));
+            t0 = fminf(fmaxf(0.99f * reach * rsqrtf(l2), kTlo), 1.0f);
+            return false;
+        }
+    }
     const int c = __float_as_int(bf.w);
     if (c < 0) return false;
     const int m = smesh[i];
-    const int32_t* cand = uniform_ptr(s_bf.bcand) + kBfCand * i;
+    const int32_t* cand = uniform_ptr(s_bf.bcand) + kBfCand * (int64_t)i;
     const float4* mbox = uniform_ptr(s_bf.mbox);
-    return backface_rule(bf.x, bf.y, bf.z, c, [cand](int j) { return cand[j]; }, xx, xy, xz, ex, ey, ez,
+    return backface_rule(bf.x, bf.y, bf.z, c & 255, unpack_below(c), [cand](int j) { return cand[j]; }, xx, xy, xz, ex, ey, ez,
                          mbox[2 * m], mbox[2 * m + 1],
                          __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(s_bf.l2max))),
                          uniform_ptr(s_bf.tris));
@@ -1361,7 +1623,7 @@ __device__ __forceinline__ void packet_visibility(const BfArgs* bf, const BvhNod
                                                   float ey, float ez, float rx, float ry, float rz,
                                                   const float4 (&p)[SPL], const int (&otri)[SPL],
                                                   const int (&omesh)[SPL], int mode, const bool (&want)[SPL],
-                                                  bool (&occl)[SPL], TravCount& n_visits)
+                                                  const float (&t0)[SPL], bool (&occl)[SPL], TravCount& n_visits)
 {
     bool need[SPL], solid[SPL];
 #pragma unroll
@@ -1406,6 +1668,7 @@ __device__ __forceinline__ void packet_visibility(const BfArgs* bf, const BvhNod
 #pragma unroll
         for (int k = 0; k < SPL; ++k) {
             sg[k] = make_seg(p[k].x, p[k].y, p[k].z, ex, ey, ez, gx, gy, gz);
+            sg[k].t0 = t0[k];
             org[k][0] = pick(gx, p[k].x, p[k].y, p[k].z);
             org[k][1] = pick(gy, p[k].x, p[k].y, p[k].z);
             org[k][2] = pick(gz, p[k].x, p[k].y, p[k].z);
@@ -1430,6 +1693,7 @@ __device__ __forceinline__ void packet_visibility(const BfArgs* bf, const BvhNod
             int lx, ly;
             cyclic_axes(kz[k], lx, ly);
             sg[k] = make_seg(p[k].x, p[k].y, p[k].z, ex, ey, ez, lx, ly, kz[k]);
+            sg[k].t0 = t0[k];
             org[k][0] = p[k].x; org[k][1] = p[k].y; org[k][2] = p[k].z;
         }
         // child order from one lane's octant (the order affects speed, not results)
@@ -1525,7 +1789,7 @@ __device__ __forceinline__ void density_item(const DensityLaunch& a, int64_t til
         s_o4 = o4;
     }
     if (threadIdx.x < kDensityStats) s_stats[threadIdx.x] = 0u;
-    if (OCC != 0 && !ZB && threadIdx.x == 0) s_bf = BfArgs{a.bface, a.bcand, a.mbox, a.bf_tris, a.solid, a.solid_stride, a.bf_L2max};
+    if (OCC != 0 && !ZB && threadIdx.x == 0) s_bf = BfArgs{a.bface, a.bcand, a.mbox, a.bf_tris, a.hz, a.hz_reach, a.solid, a.solid_stride, a.bf_L2max};
     __syncthreads();
     uint32_t n_in = 0, n_vis = 0, n_trav = 0, n_bf = 0;  // wave-uniform counters
     TravCount n_visits;
@@ -1694,19 +1958,22 @@ __device__ __forceinline__ void density_item(const DensityLaunch& a, int64_t til
                     n_in += (uint32_t)__popcll(ballot(ZB ? in : g[k] > 0.0f));
                 }
                 bool occl[SPL];
+                float t0[SPL];  // where each segment's walk begins
 #pragma unroll
-                for (int k = 0; k < SPL; ++k) occl[k] = false;
+                for (int k = 0; k < SPL; ++k) {
+                    occl[k] = false;
+                    t0[k] = kTlo;
+                }
                 if (OCC != 0 && !ZB && a.bface && ballot(any_need) != 0) {
-                    // the back-face rule first: pairs it settles leave the packet (posed
-                    // launches: sample and eye in the sample's own mesh frame)
+                    // the rules first: pairs they settle leave the packet (posed launches: sample
+                    // and eye in the sample's own mesh frame, the back-face rule alone)
                     any_need = false;
 #pragma unroll
                     for (int k = 0; k < SPL; ++k) {
                         const uint32_t i = wave_base + (uint32_t)(k * 64 + lane);
-                        if (need[k] &&
-                            backface_occluded(s_bf, a.smesh, i, p[k].x, p[k].y, p[k].z, fr.ex, fr.ey, fr.ez)) {
-                            need[k] = false;
-                            occl[k] = true;
+                        if (need[k]) {
+                            occl[k] = settled_by_rule(s_bf, a.smesh, i, p[k].x, p[k].y, p[k].z, fr.ex, fr.ey, fr.ez, t0[k]);
+                            need[k] = !occl[k] && t0[k] < 1.0f;
                         }
                         n_bf += (uint32_t)__popcll(ballot(occl[k]));
                         any_need = any_need || need[k];
@@ -1724,7 +1991,7 @@ __device__ __forceinline__ void density_item(const DensityLaunch& a, int64_t til
                         // the walk answers the lanes it tests; lanes the back-face rule settled keep it
                         bool o1[SPL];
                         packet_visibility<SPL>(&s_bf, a.nodes, a.node_stride, a.tris, a.tri_stride, fr.ex, fr.ey, fr.ez, fr.rx,
-                                               fr.ry, fr.rz, p, otri, omesh, a.occ_mode, need, o1, n_visits);
+                                               fr.ry, fr.rz, p, otri, omesh, a.occ_mode, need, t0, o1, n_visits);
 #pragma unroll
                         for (int k = 0; k < SPL; ++k) occl[k] = occl[k] || o1[k];
                         ++n_trav;
@@ -1773,7 +2040,7 @@ __device__ __forceinline__ void density_item(const DensityLaunch& a, int64_t til
                             bool o2[SPL];
                             packet_visibility<SPL>(nullptr, a.blas_nodes + b.node_base, b.node_count, a.blas_tris + b.tri_base,
                                                    b.tri_count, fo.ex, fo.ey, fo.ez, fo.rx, fo.ry, fo.rz, q, otri, omesh,
-                                                   2, rest, o2, n_visits);
+                                                   2, rest, t0, o2, n_visits);
 #pragma unroll
                             for (int k = 0; k < SPL; ++k) occl[k] = occl[k] || o2[k];
                             ++n_trav;
@@ -1950,14 +2217,16 @@ __global__ void __launch_bounds__(64) k_pair_visibility(const float* __restrict_
     bool occ[1] = {false};
     const int oct = (signbit(dx) ? 1 : 0) | (signbit(dy) ? 2 : 0) | (signbit(dz) ? 4 : 0);
     if (bf.closed && mode != 0) {
-        float nx, ny, nz;
+        float nx, ny, nz, below;
         int cnt, cand[kBfCand];
-        backface_point(px, py, pz, t, me, lane == 0, bf.V, bf.I, bf.closed, nodes, tris, bf.rmax, nx, ny, nz, cnt,
+        backface_point(px, py, pz, t, me, lane == 0, bf.V, bf.I, bf.closed, nodes, tris, bf.rmax, nx, ny, nz, below, cnt,
                        cand);
-        if (lane == 0 && me >= 0 &&
-            backface_rule(nx, ny, nz, cnt, [&cand](int j) { return cand[j]; }, px, py, pz, ex, ey, ez,
-                          bf.mbox[2 * me], bf.mbox[2 * me + 1], bf.l2max, tris)) {
-            vis[i] = 0;
+        const int packed = pack_neighbours(cnt, below);
+        const bool back = lane == 0 && me >= 0 &&
+                          backface_rule(nx, ny, nz, cnt, unpack_below(packed), [&cand](int j) { return cand[j]; }, px, py, pz, ex, ey, ez,
+                                        bf.mbox[2 * me], bf.mbox[2 * me + 1], bf.l2max, tris);
+        if (ballot(back) != 0) {
+            if (lane == 0) vis[i] = 0;
             return;
         }
     }
@@ -2130,6 +2399,16 @@ void launch_backface_prep(const float4* spos, const int32_t* smesh, int64_t n, c
         const int64_t waves = (n + (int64_t(1) << lg) - 1) >> lg;
         k_backface_prep<<<blocks(waves * 64, 256), 256, 0, s>>>(spos, smesh, n, V, I, closed, nodes, tris, rmax, lg,
                                                                 bface, bcand);
+    }
+}
+
+void launch_horizon(const float4* spos, const float4* bface, int64_t n, const BvhNode* nodes, const BvhTri* tris,
+                    float reach, float* hz, hipStream_t s)
+{
+    if (n > 0) {
+        const int lg = prep_lanes_log2(n);
+        const int64_t waves = (n + (int64_t(1) << lg) - 1) >> lg;
+        k_horizon<<<blocks(waves * 64, 256), 256, 0, s>>>(spos, bface, n, nodes, tris, reach, lg, hz);
     }
 }
 

@@ -53,9 +53,13 @@ struct gm_map {
     // stream) and the gathered launch wait for it, so pending blocks are complete whichever
     // streams queued them
     hipEvent_t added = nullptr;
+    // recorded after the points' horizons, computed by the first launch that they pay for;
+    // later launches (on any stream) wait for it
+    hipEvent_t horizon = nullptr;
     ~gm_map()
     {
         if (added) (void)hipEventDestroy(added);
+        if (horizon) (void)hipEventDestroy(horizon);
     }
 };
 
@@ -134,12 +138,30 @@ gm_status check_map(const gm_map* m)
     return GM_OK;
 }
 
+// the horizons of a plain map's points, before a launch over F records on s
+gm_status map_horizon(gm_map* m, int64_t F, hipStream_t s)
+{
+    if (m->w.horizon) {
+        GM_HIP(hipStreamWaitEvent(s, m->horizon, 0));
+        return GM_OK;
+    }
+    if (m->n <= 0 || !horizon_pays(F, m->sigma, m->mode)) return GM_OK;
+    gm_status st = GM_OK;
+    if (!m->w.backface) st = density_backface(m->scene, m->w, m->n, m->mode, true, s);
+    if (st == GM_OK && !m->horizon) GM_HIP(hipEventCreateWithFlags(&m->horizon, hipEventDisableTiming));
+    if (st == GM_OK) st = density_horizon(m->scene, m->w, m->n, s);
+    if (st == GM_OK) GM_HIP(hipEventRecord(m->horizon, s));
+    return st;
+}
+
 // one density launch over the pending records of a plain map
 gm_status map_flush(gm_map* m, hipStream_t s)
 {
     if (m->pending_hi == 0) return GM_OK;
     GM_HIP(hipStreamWaitEvent(s, m->added, 0));
     if (m->n > 0) {
+        gm_status st = map_horizon(m, m->pending_hi, s);
+        if (st != GM_OK) return st;
         DensityLaunch a;
         density_args(m->scene, m->w, m->n, (int32_t)m->pending_hi, m->sigma, m->mode, m->spl, 0, a);
         a.fix = m->pending.as<FixRec>();
@@ -260,7 +282,7 @@ gm_status gm_map_create(gm_scene* sc, const float* pos, const int32_t* tri, cons
     fill_u32(m->w.fx_shift.p, 1, (uint32_t)m->shift, s);
     if (!posed) {
         density_sort(sc, m->w, pos, tri, mesh, n, s);
-        st = density_backface(sc, m->w, n, m->mode, s);
+        st = density_backface(sc, m->w, n, m->mode, false, s);
         if (st != GM_OK) {
             delete m;
             return st;
@@ -283,7 +305,7 @@ gm_status gm_map_create(gm_scene* sc, const float* pos, const int32_t* tri, cons
             for (int32_t k = 0; k < sc->M && st == GM_OK; ++k) {
                 const int64_t off = moff[(size_t)k], nk = moff[(size_t)k + 1] - off;
                 if (nk <= 0) continue;
-                st = density_backface(sc, m->w, nk, m->mode, s, off);
+                st = density_backface(sc, m->w, nk, m->mode, false, s, off);
                 all = all && m->w.backface;
             }
             m->w.backface = st == GM_OK && all;
@@ -325,6 +347,8 @@ gm_status gm_map_add(gm_map* m, const gm_fixations* fix, const double* time, dou
         launch_fix_select(fix->eye, fix->gaze, fix->duration, time, F, t_begin, t_end, m->sigma, kGateWiden,
                           m->w.fix.as<FixRec>(), m->live.as<unsigned int>(), c, c + 2, s);
         if (m->n > 0) {
+            st = map_horizon(m, F, s);
+            if (st != GM_OK) return st;
             DensityLaunch a;
             density_args(m->scene, m->w, m->n, F, m->sigma, m->mode, m->spl, 0, a);
             a.F_live = m->live.as<unsigned int>();

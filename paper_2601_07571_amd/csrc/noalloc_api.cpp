@@ -51,7 +51,8 @@ constexpr size_t kAccBytes = align256(8 * (size_t)kMaxPoints);
 constexpr size_t kStatsBytes = align256(8 * (size_t)gm::kDensityStats);
 constexpr size_t kBcandBytes = align256(4 * (size_t)gm::kBfCand * (size_t)kMaxPoints);
 constexpr size_t kScratchBytes = kFixBytes + kShiftBytes + kKeyBytes + 2 * kHistBytes + kScanTmpMax + kSposBytes +
-                                 2 * kKeyBytes + kAccBytes + 256 + kStatsBytes + kSposBytes + kBcandBytes;
+                                 2 * kKeyBytes + kAccBytes + 256 + kStatsBytes + kSposBytes + kBcandBytes +
+                                 kKeyBytes;
 
 __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
@@ -96,6 +97,7 @@ void borrow_work(unsigned char* base, DensityWork& w)
     take(w.stats, kStatsBytes);
     take(w.bface, kSposBytes);
     take(w.bcand, kBcandBytes);
+    take(w.hz, kKeyBytes);
 }
 
 }  // namespace

@@ -1,10 +1,14 @@
-"""The rule that settles visibility pairs by boxes inside closed meshes, on the GPU against
-the FP64 oracle (which knows none of it), on scenes made to break it.
+"""The rules that settle visibility pairs without a walk of the triangles, or shorten it, on
+the GPU against the FP64 oracle (which knows none of them), on scenes made to break them.
 
 Solid boxes: a segment that meets a box inside a closed mesh is occluded.  Bodies that are
 closed but hold outside space (a hollow shell, a jar whose mouth is narrower than a grid
 cell), a body of one box, two bodies that overlap, an eye inside a body's bounding box, the
 occluder's closed flag cleared, self occlusion (another mesh's solid must not count).
+
+Horizons: a segment steeper than everything near its point begins its walk beyond it.  Steps,
+a thin fence standing on a floor, a plate floating just above it, a groove, a floor whose
+triangles are far larger than the objects on it, and points without a known triangle.
 
 The tolerance is parity_util's: 1e-5 relative plus the oracle's own ambiguous pairs, and no
 visibility decision other than the oracle's outside its fragile set."""
@@ -153,3 +157,67 @@ def test_cleared_flag_takes_the_mesh_out_of_the_rule(gm):
     on = _check(gm, SOLIDS["one_box"](), 500.0, eye, gaze, dur, 4.0, "full")
     off = _check(gm, SOLIDS["one_box"](), 500.0, eye, gaze, dur, 4.0, "full", clear=1)
     assert on["visible"] == off["visible"] and off["triangle_tests"] > on["triangle_tests"], (on, off)
+
+
+def _wavy(u, v):
+    x, y = (u - 0.5) * 1.2, (v - 0.5) * 1.2
+    return x, y, 0.02 * np.sin(40 * x) * np.cos(35 * y)
+
+
+NEAR = {
+    "steps": lambda: [_grid(48, 48, lambda u, v: ((u - 0.5) * 1.2, (v - 0.5) * 1.2, 0.01 * np.floor(8 * u)))],
+    "waves": lambda: [_grid(64, 64, _wavy)],
+    "groove": lambda: [_grid(48, 48, lambda u, v: ((u - 0.5) * 1.2, (v - 0.5) * 1.2, 0.8 * abs(u - 0.5)))],
+    "fence": lambda: [_floor(1.2, 40), _grid(60, 2, lambda u, v: ((u - 0.5) * 1.2, 0.0003, 0.02 * v)),
+                      _grid(60, 2, lambda u, v: (0.0151, (u - 0.5) * 1.2, 0.03 * v))],
+    "plate": lambda: [_floor(1.2, 40), _grid(20, 20, lambda u, v: ((u - 0.5) * 0.4, (v - 0.5) * 0.4, 0.002))],
+    "big_floor": lambda: [_grid(1, 1, lambda u, v: ((u - 0.5) * 1.6, (v - 0.5) * 1.6, 0.0)), _sphere(0.1, (0, 0, 0.1)),
+                          _sphere(0.05, (0.2, 0.1, 0.05))],
+}
+
+
+@pytest.mark.parametrize("name", sorted(NEAR))
+def test_horizons(gm, name):
+    """160 fixations at 5 degrees (F sigma^2 = 1.2: the horizons are in use), eyes low over the
+    surface and high above it."""
+    rng = np.random.default_rng(8)
+    a = _eyes(rng, 100, (-1.2, -1.2, 0.1), (1.2, 1.2, 0.5), (0, 0, 0))
+    b = _eyes(rng, 60, (-0.5, -0.5, 1.0), (0.5, 0.5, 1.6), (0, 0, 0))
+    eye, gaze, dur = (np.concatenate(x) for x in zip(a, b))
+    _check(gm, NEAR[name](), 900.0, eye, gaze, dur, 5.0, "full")
+
+
+def test_points_without_a_triangle(gm):
+    """No own triangle: no normal, no horizon; every pair is walked, also where the point lies
+    on the surface."""
+    rng = np.random.default_rng(9)
+    eye, gaze, dur = _eyes(rng, 160, (-0.6, -0.6, 0.6), (0.6, 0.6, 1.4), (0, 0, 0))
+    _check(gm, NEAR["waves"](), 500.0, eye, gaze, dur, 5.0, "full", with_tri=False)
+
+
+def test_map_blocks_share_one_horizon(gm):
+    """An incremental map computes its points' horizons at the first launch that they pay for:
+    blocks before and after it, on two streams, give the one-call map bit for bit."""
+    import torch
+    m = workloads.sphere_mesh(freq=20, radius=0.4, displace=0.04, seed=2)
+    scene = gm.Scene([(m.V, m.I)])
+    s = scene.build_samples(2000.0, 1)
+    f = workloads.shell_fixations(np.random.default_rng(3), [m], 500, dur=(0.1, 0.5))
+    fix = gm.Fixations(f.eye, f.gaze, f.dur)
+    args = dict(theta_deg=4.0, occlusion="full", tri=s.tri, mesh=s.mesh)
+    one = gm.DensityMap(scene, s.pos, **args).add(fix).read()
+    split = gm.DensityMap(scene, s.pos, **args)
+    split.add(fix.subset(0, 40))
+    split.read()                       # too few fixations for horizons
+    split.add(fix.subset(40, 400))
+    split.read()
+    torch.cuda.synchronize()
+    other = torch.cuda.Stream()
+    with torch.cuda.stream(other):
+        split.add(fix.subset(400, 500))
+        two = split.read()
+    torch.cuda.synchronize()
+    assert float(one.max.cpu()[0]) > 0
+    assert torch.equal(one.density, two.density) and torch.equal(one.max, two.max)
+    plain = scene.accumulate(s.pos, fix, 4.0, tri=s.tri, mesh=s.mesh)
+    assert torch.equal(plain.density > 0, one.density > 0)
