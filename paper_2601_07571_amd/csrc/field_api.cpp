@@ -25,7 +25,7 @@ struct gm_field {
     DevBuf gate_d, need, qoffs, qscan, gpos, gtri, gmesh, gidx, grho, gnorm;
     DevBuf rcnt, rpart, rbase, ridx, take_d;  // routed inference: per-mesh counts, per-chunk counts,
                                               // segment starts, point lists
-    DevBuf gpart, lpart;               // training: per-wave gradient and loss slots
+    DevBuf tbuf, tsums, tpart, tse;    // training: a pass's activations, row sums, squared errors
     std::vector<float> rel_l2;
     std::vector<uint8_t> gate;
     double norm_max = 0.0;
@@ -37,7 +37,7 @@ struct gm_field {
     {
         for (DevBuf* b : {&master, &m, &v, &grad, &blob, &loss, &flag, &sel, &offs, &idx, &scan_tmp, &pred, &l2sums,
                           &l2part, &geom_d, &net_off, &net_cnt, &gate_d, &need, &qoffs, &qscan, &gpos, &gtri, &gmesh,
-                          &gidx, &grho, &gnorm, &rcnt, &rpart, &rbase, &ridx, &take_d, &gpart, &lpart})
+                          &gidx, &grho, &gnorm, &rcnt, &rpart, &rbase, &ridx, &take_d, &tbuf, &tsums, &tpart, &tse})
             b->release();
     }
 };
@@ -103,6 +103,22 @@ gm_status infer_routed(gm_field* f, const float* pos, int64_t q, float* out, con
                               pb > 0 ? f->rpart.as<unsigned int>() : nullptr, f->rbase.as<int64_t>(),
                               f->ridx.as<int32_t>(), s);
     GM_HIP(hipGetLastError());
+    return GM_OK;
+}
+
+// scratch of training over `batch` points and M networks
+gm_status train_scratch(gm_field* f, int32_t batch, int32_t M, FieldTrain& t)
+{
+    size_t buf, sums, se;
+    field_train_bytes(batch, M, buf, sums, se);
+    GM_HIP(f->tbuf.ensure(buf));
+    GM_HIP(f->tsums.ensure(sums));
+    GM_HIP(f->tpart.ensure(sums));
+    GM_HIP(f->tse.ensure(se));
+    t.buf = f->tbuf.as<unsigned char>();
+    t.sums = f->tsums.as<float>();
+    t.part = f->tpart.as<float>();
+    t.se = f->tse.as<float>();
     return GM_OK;
 }
 
@@ -222,10 +238,9 @@ gm_status gm_field_gradient(gm_field* f, int32_t net, const float* pos, const fl
     if (st != GM_OK) return st;
     hipStream_t s = nullptr;
     float* gnet = f->grad.as<float>() + (size_t)net * kFieldParams;
-    const int32_t slots = field_train_slots((int32_t)n, 1);
-    GM_HIP(f->gpart.ensure(sizeof(float) * kFieldParams * (size_t)slots));
-    GM_HIP(f->lpart.ensure(sizeof(double) * (size_t)slots));
     FieldTrain t;
+    st = train_scratch(f, (int32_t)n, 1, t);
+    if (st != GM_OK) return st;
     t.pos = pos;
     t.target = target;
     t.idx = nullptr;
@@ -234,9 +249,7 @@ gm_status gm_field_gradient(gm_field* f, int32_t net, const float* pos, const fl
     t.inv_batch = (float)(1.0 / (double)n);
     t.key0 = t.key1 = 0;
     t.step = 0;
-    t.gpart = f->gpart.as<float>();
-    t.lpart = f->lpart.as<double>();
-    launch_field_train(net_blob(f, net), f->geom[(size_t)net], t, gnet, f->loss.as<double>(), s);
+    launch_field_gradient(net_blob(f, net), f->geom[(size_t)net], t, gnet, f->loss.as<double>(), s);
     GM_HIP(hipGetLastError());
     double l = 0.0;
     GM_HIP(hipMemcpy(grad, gnet, sizeof(float) * kFieldParams, hipMemcpyDeviceToHost));
@@ -333,21 +346,16 @@ gm_status gm_field_train(gm_field* f, const float* pos, const int32_t* mesh, con
     t.inv_batch = 1.0f / (float)P->batch;
     t.key0 = key0 ^ 0x5bd1e995u;
     t.key1 = key1 ^ 0x1b873593u;
-    const int32_t slots = field_train_slots(P->batch, M);
-    GM_HIP(f->gpart.ensure(sizeof(float) * kFieldParams * (size_t)slots * (size_t)M));
-    GM_HIP(f->lpart.ensure(sizeof(double) * (size_t)slots * (size_t)M));
-    t.gpart = f->gpart.as<float>();
-    t.lpart = f->lpart.as<double>();
+    st = train_scratch(f, P->batch, M, t);
+    if (st != GM_OK) return st;
     for (int32_t it = 0; it < P->steps && total > 0; ++it) {
         t.step = (uint32_t)it;
-        launch_field_train_nets(f->blob.as<unsigned char>(), nets, M, t, f->grad.as<float>(), f->loss.as<double>(), s);
         const double frac = P->steps > 1 ? (double)it / (double)(P->steps - 1) : 1.0;
         const double lr = P->lr_final + 0.5 * (P->lr - P->lr_final) * (1.0 + std::cos(M_PI * frac));
         float c1, c2;
         adam_bias_scales(it + 1, P->beta1, P->beta2, c1, c2);
-        launch_field_adam(f->master.as<float>(), f->m.as<float>(), f->v.as<float>(), f->grad.as<float>(),
-                          (int64_t)M * kFieldParams, (float)lr, P->beta1, P->beta2, P->eps, c1, c2, s);
-        launch_field_pack_nets(f->master.as<float>(), f->blob.as<unsigned char>(), M, s);
+        launch_field_step(f->blob.as<unsigned char>(), nets, M, t, f->master.as<float>(), f->m.as<float>(),
+                          f->v.as<float>(), (float)lr, P->beta1, P->beta2, P->eps, c1, c2, f->loss.as<double>(), s);
     }
     GM_HIP(hipGetLastError());
     if (P->steps > 0 && total > 0) {

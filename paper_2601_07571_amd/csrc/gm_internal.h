@@ -310,9 +310,10 @@ struct FieldTrain {
     float inv_batch;         // 1 / batch
     uint32_t key0, key1;     // Philox key of the batch draw
     uint32_t step;
-    float* gpart;            // [slots][kFieldParams] per-wave gradient sums (per network)
-    double* lpart;           // [slots] per-wave sums of squared errors (per network)
-    int32_t slots;           // set by the launchers: field_train_slots(batch, networks)
+    unsigned char* buf;      // activations and dZ of one pass's tiles (field_train_bytes)
+    float* sums;             // [networks][8][kFieldParams] row sums of the gradient
+    float* part;             // the same size: the slot in progress between passes
+    float* se;               // [networks][tiles] squared errors
 };
 
 // Several networks in one launch (blockIdx.y = network): geometry, and the start and
@@ -325,7 +326,6 @@ struct FieldNets {
     int64_t pack_stride = 0;
 };
 
-void launch_field_pack(const float* master, unsigned char* blob, hipStream_t s);
 // the packed images of M networks (parameters kFieldParams apart, images field_pack_bytes() apart)
 void launch_field_pack_nets(const float* master, unsigned char* blob, int32_t M, hipStream_t s);
 // Points whose mesh (mesh[i], else tri_mesh[tri[i]] for 0 <= tri[i] < T) is `m` get the
@@ -353,16 +353,18 @@ void launch_field_infer_routed(const unsigned char* blobs, int64_t pack_stride, 
                                int32_t* ridx, hipStream_t s);
 // sel[i] = flag[i] && mesh[i] == m
 void launch_field_select(const uint32_t* flag, const int32_t* mesh, int32_t m, int64_t n, uint32_t* sel, hipStream_t s);
-// One training step's forward and backward pass: the gradient grad [kFieldParams] and the
-// sum of squared errors loss [1], reduced in a fixed order from the per-wave slots
-// t.gpart / t.lpart (field_train_slots(batch, 1) of them).
-int32_t field_train_slots(int32_t batch, int32_t M);
-void launch_field_train(const unsigned char* blob, const FieldGeom& g, FieldTrain t, float* grad, double* loss,
-                        hipStream_t s);
-// the same for M networks at once (see FieldNets; t.key0 is xored with the network):
-// grad [M][kFieldParams], loss [M], slots field_train_slots(batch, M) per network
-void launch_field_train_nets(const unsigned char* blob, const FieldNets& nets, int32_t M, FieldTrain t, float* grad,
-                             double* loss, hipStream_t s);
+// Scratch of a training step or gradient over `batch` points and M networks: bytes of
+// FieldTrain::buf, sums (and part) and se.
+void field_train_bytes(int32_t batch, int32_t M, size_t& buf, size_t& sums, size_t& se);
+// The gradient grad [kFieldParams] and sum of squared errors loss [1] of one network over the
+// first t.batch points (or a drawn batch), every sum in an order fixed by the batch.
+void launch_field_gradient(const unsigned char* blob, const FieldGeom& g, const FieldTrain& t, float* grad, double* loss,
+                           hipStream_t s);
+// One training step of M networks (see FieldNets; t.key0 is xored with the network): their
+// gradients, summed as above, one Adam update of master, m and v, the packed images of the
+// new weights and the step's losses [M].
+void launch_field_step(unsigned char* blob, const FieldNets& nets, int32_t M, const FieldTrain& t, float* master, float* m,
+                       float* v, float lr, float b1, float b2, float eps, float c1, float c2, double* loss, hipStream_t s);
 void launch_field_adam(float* master, float* m, float* v, float* grad, int64_t count, float lr, float b1, float b2,
                        float eps, float c1, float c2, hipStream_t s);
 // held-out split and per-mesh error sums

@@ -11,12 +11,12 @@
 // in the slot order of slot_feature(); the packed weight image stores every
 // matrix in that order, so activations never leave registers between layers.
 // The backward pass reuses the same trick for dH = W dZ and takes the weight
-// gradients dW = H dZ^T as MFMA products over the 32 points of the wave (a
-// transpose of H and dZ through per-wave LDS tiles).  Each wave adds its tiles'
-// gradients, in its own tile order, into a slot of its own (plain loads and stores,
-// no atomics), and a second kernel sums the slots in slot order: the gradient, and
-// so training, is the same bit for bit on every run.  Adam (Kingma and Ba 2015)
-// keeps fp32 master weights and moments.
+// gradients dW = H dZ^T as MFMA products over the 32 points of a tile: the first kernel
+// of a step leaves every tile's H and dZ in memory, transposed (features in rows) through
+// per-wave LDS, and the second multiplies them tile by tile and adds the products in a
+// fixed order (no atomics), so the gradient, and training, is the same bit for bit on every
+// run.  The third adds the partial sums, takes the Adam step (Kingma and Ba 2015; fp32
+// master weights and moments) and writes the BF16 image of the new weights.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -166,10 +166,29 @@ __device__ __forceinline__ float field_forward(const unsigned char* lds, const F
     return part + __shfl_xor(part, 32, 64) + *reinterpret_cast<const float*>(lds + kOffB5);
 }
 
-__device__ __forceinline__ void stage(unsigned char* dst, const unsigned char* __restrict__ src, int bytes)
+// A workgroup's copy of the packed weights to LDS, ten 16-byte loads of a thread in flight
+// before their stores (k_field_infer_routed 101 -> 97 us for 500,003 points; more of them
+// cost registers that the caller needs).
+template <int Threads, int Bytes>
+__device__ __forceinline__ void stage(unsigned char* dst, const unsigned char* __restrict__ src)
 {
-    for (int o = threadIdx.x * 16; o < bytes; o += kThreads * 16)
-        *reinterpret_cast<uint4*>(dst + o) = *reinterpret_cast<const uint4*>(src + o);
+    constexpr int kFull = Bytes / (16 * Threads);
+    constexpr int kAtOnce = 10;
+    const int t = 16 * (int)threadIdx.x;
+    const int tail = 16 * kFull * Threads + t;
+    uint4 last = make_uint4(0, 0, 0, 0);
+    if (tail < Bytes) last = *reinterpret_cast<const uint4*>(src + tail);
+#pragma unroll
+    for (int g = 0; g < kFull; g += kAtOnce) {
+        uint4 v[kAtOnce];
+#pragma unroll
+        for (int k = 0; k < kAtOnce; ++k)
+            if (g + k < kFull) v[k] = *reinterpret_cast<const uint4*>(src + 16 * (g + k) * Threads + t);
+#pragma unroll
+        for (int k = 0; k < kAtOnce; ++k)
+            if (g + k < kFull) *reinterpret_cast<uint4*>(dst + 16 * (g + k) * Threads + t) = v[k];
+    }
+    if (tail < Bytes) *reinterpret_cast<uint4*>(dst + tail) = last;
 }
 
 // ---------------------------------------------------------------------------
@@ -222,7 +241,7 @@ __global__ void __launch_bounds__(kThreads) k_field_infer(const unsigned char* _
                                                           float* __restrict__ out, FieldRoute route)
 {
     __shared__ __attribute__((aligned(16))) unsigned char s_blob[kInfer];
-    stage(s_blob, blob, kInfer);
+    stage<kThreads, kInfer>(s_blob, blob);
     __syncthreads();
     const int lane = __lane_id(), wave = threadIdx.x >> 6;
     const int64_t tiles = (q + 31) / 32;
@@ -264,12 +283,6 @@ __global__ void __launch_bounds__(kThreads) k_field_infer(const unsigned char* _
 // when the network changes (its groups run in mesh order).
 constexpr int kGroup = 32 * (kThreads / 64);
 
-__global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v)
-{
-    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
 __device__ __forceinline__ int group_mesh(const int64_t* __restrict__ base, int32_t M, int64_t first)
 {
     int lo = 0, hi = M - 1;  // last m with base[m] <= first
@@ -302,7 +315,7 @@ __global__ void __launch_bounds__(kThreads) k_field_infer_routed(const unsigned 
         const int m = group_mesh(base, M, gi * kGroup);
         if (m != staged) {
             __syncthreads();
-            stage(s_blob, blobs + (int64_t)m * pack_stride, kInfer);
+            stage<kThreads, kInfer>(s_blob, blobs + (int64_t)m * pack_stride);
             __syncthreads();
             staged = m;
             g = geoms[m];
@@ -510,226 +523,470 @@ __global__ void __launch_bounds__(kThreads) k_route_scatter(const int32_t* __res
     }
 }
 
-// a wave's gradient slot: its first tile writes, the later ones add (one lane per entry);
-// ONE: every wave takes at most one tile, so every write is the first
-template <bool ONE>
-__device__ __forceinline__ void put(float* p, float v, bool first) { *p = ONE || first ? v : *p + v; }
+// ---------------------------------------------------------------------------
+// One training step.  The batch is cut into tiles of 32 points, `slots` of them at a time:
+// tile w + k slots is the k-th of slot w (usually there is one per slot).  The gradient of a
+// parameter is the sum over the slots, each the sum of its tiles' in order, taken in eight
+// rows of consecutive slots: every row in slot order, then the rows in order.  That order is
+// fixed by (batch, networks) alone.
+//
+//   k_field_tiles  a wave per tile: forward, dZ of every layer, and to memory the features
+//                  and hidden activations H and the dZ, BF16, features in rows (what the
+//                  products below read), and the tile's sums for the biases and the output
+//                  layer (kAux floats);
+//   k_field_dw     a workgroup per (network, row, half layer), a wave per 32 x 32 block of
+//                  the layer's weights: H dZ^T of each tile by two matrix products, added to
+//                  the row's sum in slot order;
+//   k_field_step   a thread per parameter: the rows, Adam, the new BF16 images.
+//
+// Only activations go through memory (35 KB a tile) instead of a whole gradient (75 KB a
+// tile, written and read again): 4 networks x 16,384 points take 118 -> 43 us a step, one
+// network 51 -> 38 us.
+// ---------------------------------------------------------------------------
+constexpr int kRows = 8;
+// a workgroup stages a network's 70 KB image once for this many tiles (512 tiles on 256 CUs:
+// 19.9 us with eight, 27.5 with four, 27.0 with two; 33 tiles: 15.0, 21.9, 22.0)
+constexpr int kTileWaves = 8;
+constexpr int kDzBytes = kW * 64;                  // one dZ or H of 64 features x 32 points
+constexpr int kX0Bytes = kFieldFeat * 64;          // the 96 input features
+constexpr int kOffDz = 0;                          // dZ of layers 1..4
+constexpr int kOffX0 = 4 * kDzBytes;               // input features (slot order)
+constexpr int kOffH = kOffX0 + kX0Bytes;           // hidden layers 1..3
+constexpr int kOffAux = kOffH + 3 * kDzBytes;      // biases of layers 1..4, w5, b5
+constexpr int kAux = 4 * kW + kW + 1;
+constexpr int kTileBytes = kOffAux + (kAux + 3) / 4 * 16;
 
-template <bool ONE>
-__global__ void __launch_bounds__(kThreads) k_field_train(const unsigned char* __restrict__ blob, FieldGeom g,
-                                                          FieldTrain t, FieldNets nets)
+// row r, position q of a network: the tile, or -1; positions run through the row's slots,
+// `rounds` tiles each
+struct TileOrder {
+    int32_t tiles, slots, used, per, rounds;
+};
+
+__device__ __forceinline__ int tile_at(const TileOrder& o, int r, int q)
 {
+    const int w = r * o.per + q / o.rounds, k = q % o.rounds;
+    if (w >= min(o.used, (r + 1) * o.per)) return -1;
+    const int64_t tile = (int64_t)w + (int64_t)k * o.slots;
+    return tile < o.tiles ? (int)tile : -1;
+}
+
+// A lane holds two neighbouring features of its point n, as packed BF16 (the even one low);
+// it gets the two points n & ~1 and n | 1 of one feature, the even one in even lanes and the
+// odd one in odd lanes: transposed rows are then written four bytes at a time.
+__device__ __forceinline__ unsigned pair_points(unsigned x, unsigned sel)
+{
+    const unsigned y = __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xf, 0xf, true);  // the neighbour's (quad_perm 1, 0, 3, 2)
+    return __builtin_amdgcn_perm(y, x, sel);
+}
+
+// the pairs of a run of 8 features in registers, feature row0 + 0 .. 7 (row0 + 4 after every
+// four when `split`: the accumulator's row order), put(row of the pair, value)
+template <bool Split, class Put>
+__device__ __forceinline__ void pairs8(const bf16x8& f, int row0, unsigned sel, const Put& put)
+{
+    const u32x4 u = __builtin_bit_cast(u32x4, f);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) put(row0 + 2 * k + (Split && k >= 2 ? 4 : 0), pair_points(u[k], sel));
+}
+
+// 32 R feature rows of 32 points from LDS to memory, in the operand order of the products:
+// per 32 rows 2 KB, [half of the points][half of those][row][8 points], so that both this
+// wave's stores and the next kernel's loads are whole kilobytes
+template <int R>
+__device__ __forceinline__ void rows_out(const __bf16 (*tr)[kTileStride], unsigned char* dst, int lane)
+{
+#pragma unroll
+    for (int c = 0; c < 2 * R; ++c) {
+        const int row = 32 * (c >> 1) + (lane & 31), part = 2 * (c & 1) + (lane >> 5);
+        *reinterpret_cast<uint4*>(dst + 1024 * c + 16 * lane) = *reinterpret_cast<const uint4*>(&tr[row][8 * part]);
+    }
+}
+
+__global__ void __launch_bounds__(64 * kTileWaves) k_field_tiles(const unsigned char* __restrict__ blob, FieldGeom g,
+                                                              FieldTrain t, FieldNets nets, TileOrder ord,
+                                                              int q0, int Q, unsigned char* __restrict__ buf)
+{
+    const int net = blockIdx.y;
     if (nets.off) {
         // network blockIdx.y of several trained in one launch
-        const int m = blockIdx.y;
-        const int64_t c = nets.cnt[m];
+        const int64_t c = nets.cnt[net];
         if (c == 0) return;
-        blob += (int64_t)m * nets.pack_stride;
-        g = nets.geom[m];
-        t.idx += nets.off[m];
+        blob += (int64_t)net * nets.pack_stride;
+        g = nets.geom[net];
+        t.idx += nets.off[net];
         t.n_idx = c;
-        t.key0 ^= (uint32_t)m;
-        t.gpart += (int64_t)m * t.slots * kFieldParams;
-        t.lpart += (int64_t)m * t.slots;
+        t.key0 ^= (uint32_t)net;
     }
     __shared__ __attribute__((aligned(16))) unsigned char s_blob[kPack];
-    __shared__ __attribute__((aligned(16))) __bf16 s_dz[kThreads / 64][kW][kTileStride];
-    __shared__ __attribute__((aligned(16))) __bf16 s_h[kThreads / 64][kFieldFeat][kTileStride];
-    stage(s_blob, blob, kPack);
+    __shared__ __attribute__((aligned(16))) __bf16 s_tr[kTileWaves][kW][kTileStride];
+    stage<64 * kTileWaves, kPack>(s_blob, blob);
     __syncthreads();
-    const int lane = __lane_id(), wave = threadIdx.x >> 6;
+    const int lane = __lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 31, h = lane >> 5;
+    const int b = blockIdx.x * kTileWaves + wave;  // row-major over (row, position)
+    if (b >= kRows * Q) return;
+    const int tile = tile_at(ord, b / Q, q0 + b % Q);
+    if (tile < 0) return;
+    unsigned char* out = buf + ((int64_t)net * kRows * Q + b) * kTileBytes;
+    float* aux = reinterpret_cast<float*>(out + kOffAux);
+    __bf16(*tr)[kTileStride] = s_tr[wave];
     const float* w5 = reinterpret_cast<const float*>(s_blob + kOffW5);
-    const int tiles = (t.batch + 31) / 32;
-    for (int tile = blockIdx.x * (kThreads / 64) + wave; tile < tiles; tile += gridDim.x * (kThreads / 64)) {
-        asm volatile("" ::: "memory");  // weights stay in LDS (see k_field_infer)
-        // this wave's gradient slot (blockIdx.x * waves + wave < t.slots), written by its
-        // first tile and added to by the later ones; a fresh copy of the base each tile:
-        // otherwise the ~300 lane-dependent addresses below are hoisted out of the loop
-        // and spilled
-        const int slot = __builtin_amdgcn_readfirstlane(blockIdx.x * (kThreads / 64) + wave);
-        const bool first = tile == slot;
-        float* grad = t.gpart + (int64_t)slot * kFieldParams;
-        asm volatile("" : "+s"(grad));
-        const int j = tile * 32 + n;
-        const bool ok = j < t.batch;
-        int64_t i = ok ? j : 0;
-        if (t.idx) {
-            uint32_t c0 = (uint32_t)j, c1 = t.step, c2 = 0u, c3 = 4u;
-            philox4x32_10(c0, c1, c2, c3, t.key0, t.key1);
-            i = t.idx[(int64_t)(((uint64_t)c0 * (uint64_t)t.n_idx) >> 32)];
-        }
-        Acts A;
-        const float o = field_forward(s_blob, g, t.pos[3 * i], t.pos[3 * i + 1], t.pos[3 * i + 2], lane, A);
-        const float y = softplus(o);
-        const float diff = ok ? y - t.target[i] : 0.0f;
-        const float dO = __fdividef(2.0f * diff * t.inv_batch, 1.0f + __expf(-o));  // d loss / d o
-        // loss and the output-layer gradients, reduced over the 32 points of the wave
-        float se = h == 0 ? diff * diff : 0.0f, sb = h == 0 ? dO : 0.0f;
+    const int64_t j = (int64_t)tile * 32 + n;
+    const bool ok = j < t.batch;
+    int64_t i = ok ? j : 0;
+    if (t.idx) {
+        uint32_t c0 = (uint32_t)j, c1 = t.step, c2 = 0u, c3 = 4u;
+        philox4x32_10(c0, c1, c2, c3, t.key0, t.key1);
+        i = t.idx[(int64_t)(((uint64_t)c0 * (uint64_t)t.n_idx) >> 32)];
+    }
+    Acts A;
+    const float o = field_forward(s_blob, g, t.pos[3 * i], t.pos[3 * i + 1], t.pos[3 * i + 2], lane, A);
+    const float y = softplus(o);
+    const float diff = ok ? y - t.target[i] : 0.0f;
+    const float dO = __fdividef(2.0f * diff * t.inv_batch, 1.0f + __expf(-o));  // d loss / d o
+    // loss and the output bias' gradient, reduced over the 32 points of the wave
+    float se = h == 0 ? diff * diff : 0.0f, sb = h == 0 ? dO : 0.0f;
 #pragma unroll
-        for (int d = 1; d < 32; d <<= 1) {
-            se += __shfl_xor(se, d, 64);
-            sb += __shfl_xor(sb, d, 64);
-        }
-        if (lane == 0) {
-            t.lpart[slot] = ONE || first ? (double)se : t.lpart[slot] + (double)se;
-            put<ONE>(&grad[kFieldOffB5], sb, first);
-        }
+    for (int d = 1; d < 32; d <<= 1) {
+        se += __shfl_xor(se, d, 64);
+        sb += __shfl_xor(sb, d, 64);
+    }
+    if (lane == 0) {
+        t.se[(int64_t)net * ord.tiles + tile] = se;
+        aux[5 * kW] = sb;
+    }
+    {
+        // the output weights' gradients: 32 sums over the 32 points, the pairwise tree over
+        // the lanes' bits; each step halves the values a lane still carries, so lane n ends
+        // with the sum of the value whose index is n's bits reversed
+        float v[32];
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-            for (int jj = 0; jj < 8; ++jj) {
-                float gw = (float)A.h[3][ks][jj] * dO;
+            for (int jj = 0; jj < 8; ++jj) v[8 * ks + jj] = (float)A.h[3][ks][jj] * dO;
 #pragma unroll
-                for (int d = 1; d < 32; d <<= 1) gw += __shfl_xor(gw, d, 64);
-                if (n == 0) put<ONE>(&grad[kFieldOffW5 + 16 * ks + slot_feature(8 * h + jj)], gw, first);
+        for (int d = 0; d < 5; ++d) {
+            const int half = 16 >> d;
+            const bool up = (n >> d) & 1;
+#pragma unroll
+            for (int k = 0; k < half; ++k) {
+                const float keep = up ? v[half + k] : v[k], give = up ? v[k] : v[half + k];
+                v[k] = keep + __shfl_xor(give, 1 << d, 64);
             }
+        }
+        const int idx = ((n & 1) << 4) | ((n & 2) << 2) | (n & 4) | ((n & 8) >> 2) | ((n & 16) >> 4);
+        // value idx = 8 ks + jj is feature 16 ks + slot_feature(8 h + jj)
+        const int sl = 8 * h + (idx & 7);
+        aux[4 * kW + 16 * (idx >> 3) + ((sl & 7) < 4 ? 4 * (sl >> 3) + (sl & 7) : 8 + 4 * (sl >> 3) + (sl & 7) - 4)] = v[0];
+    }
+    // input features and hidden layers 1..3, transposed through the wave's LDS rows
+    const unsigned sel = (n & 1) ? 0x03020706u : 0x05040100u;
+    unsigned char* pt = reinterpret_cast<unsigned char*>(&tr[n & 1][n & 30]);
+    const auto put8 = [pt, h](int row, unsigned v) { *reinterpret_cast<unsigned*>(pt + 2 * kTileStride * (row + 8 * h)) = v; };
+    const auto put4 = [pt, h](int row, unsigned v) { *reinterpret_cast<unsigned*>(pt + 2 * kTileStride * (row + 4 * h)) = v; };
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) pairs8<false>(A.x0[ks], 16 * ks, sel, put8);
+    asm volatile("" ::: "memory");
+    rows_out<2>(tr, out + kOffX0, lane);
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int ks = 4; ks < 6; ++ks) pairs8<false>(A.x0[ks], 16 * (ks - 4), sel, put8);
+    asm volatile("" ::: "memory");
+    rows_out<1>(tr, out + kOffX0 + kDzBytes, lane);
+#pragma unroll
+    for (int L = 0; L < 3; ++L) {
         asm volatile("" ::: "memory");
-        // dZ of layer 4 in the accumulator layout
-        f32x16 dz0, dz1;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) pairs8<true>(A.h[L][ks], 16 * ks, sel, put4);
+        asm volatile("" ::: "memory");
+        rows_out<2>(tr, out + kOffH + L * kDzBytes, lane);
+    }
+    // dZ of layer 4 in the accumulator layout
+    f32x16 dz0, dz1;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int f = 8 * (v >> 2) + 4 * h + (v & 3);
+        dz0[v] = (float)A.h[3][v >> 3][v & 7] > 0.0f ? w5[f] * dO : 0.0f;
+        dz1[v] = (float)A.h[3][2 + (v >> 3)][v & 7] > 0.0f ? w5[32 + f] * dO : 0.0f;
+    }
+#pragma unroll
+    for (int L = 4; L >= 1; --L) {
+        asm volatile("" ::: "memory");  // one layer at a time (bounds register pressure)
+        bf16x8 dzb[4];
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            const int f = 8 * (v >> 2) + 4 * h + (v & 3);
-            dz0[v] = (float)A.h[3][v >> 3][v & 7] > 0.0f ? w5[f] * dO : 0.0f;
-            dz1[v] = (float)A.h[3][2 + (v >> 3)][v & 7] > 0.0f ? w5[32 + f] * dO : 0.0f;
+            dzb[v >> 3][v & 7] = (__bf16)dz0[v];
+            dzb[2 + (v >> 3)][v & 7] = (__bf16)dz1[v];
         }
 #pragma unroll
-        for (int L = 4; L >= 1; --L) {
-            asm volatile("" ::: "memory");  // one layer at a time (bounds register pressure)
-            bf16x8 dzb[4];
+        for (int k = 0; k < 4; ++k) pairs8<true>(dzb[k], 16 * k, sel, put4);
+        asm volatile("" ::: "memory");
+        rows_out<2>(tr, out + kOffDz + (L - 1) * kDzBytes, lane);
+        {
+            // bias gradient: row sums of dZ over the points in order (lane = output feature)
+            float sbias = 0.0f;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const bf16x8 d8 = *reinterpret_cast<const bf16x8*>(&tr[lane][8 * c]);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) sbias += (float)d8[k];
+            }
+            aux[(L - 1) * kW + lane] = sbias;
+        }
+        if (L >= 2) {
+            const unsigned char* Bm = s_blob + kOffB2 + (L - 2) * kMatH;
+            f32x16 e0 = {}, e1 = {};
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                e0 = mfma(lds8(Bm, n * kSH + 16 * ks + 8 * h), dzb[ks], e0);
+                e1 = mfma(lds8(Bm, (32 + n) * kSH + 16 * ks + 8 * h), dzb[ks], e1);
+            }
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                dzb[v >> 3][v & 7] = (__bf16)dz0[v];
-                dzb[2 + (v >> 3)][v & 7] = (__bf16)dz1[v];
-                const int f = 8 * (v >> 2) + 4 * h + (v & 3);
-                s_dz[wave][f][n] = dzb[v >> 3][v & 7];
-                s_dz[wave][32 + f][n] = dzb[2 + (v >> 3)][v & 7];
-            }
-            if (L >= 2) {
-#pragma unroll
-                for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-                    for (int jj = 0; jj < 8; ++jj) s_h[wave][16 * ks + slot_feature(8 * h + jj)][n] = A.h[L - 2][ks][jj];
-            } else {
-#pragma unroll
-                for (int ks = 0; ks < 6; ++ks)
-#pragma unroll
-                    for (int jj = 0; jj < 8; ++jj) s_h[wave][16 * ks + 8 * h + jj][n] = A.x0[ks][jj];
-            }
-            asm volatile("" ::: "memory");
-            // weight gradient dW[k][i] = sum over points of H[k][p] dZ[i][p]
-            const int nk = L == 1 ? 3 : 2;
-#pragma unroll
-            for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-                for (int nb = 0; nb < 3; ++nb) {
-                    if (nb >= nk) break;
-                    f32x16 c = {};
-#pragma unroll
-                    for (int kp = 0; kp < 2; ++kp) {
-                        const bf16x8 a = *reinterpret_cast<const bf16x8*>(&s_dz[wave][mb * 32 + n][16 * kp + 8 * h]);
-                        const bf16x8 b = *reinterpret_cast<const bf16x8*>(&s_h[wave][nb * 32 + n][16 * kp + 8 * h]);
-                        c = mfma(a, b, c);
-                    }
-                    const int krow = L == 1 ? input_feature(nb * 32 + n) : nb * 32 + n;
-                    float* gW = grad + kFieldOffW[L] + krow * kW + mb * 32 + 4 * h;
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) put<ONE>(gW + 8 * (v >> 2) + (v & 3), c[v], first);
-                }
-            // bias gradient: row sums of dZ (lane = output feature)
-            {
-                float sbias = 0.0f;
-#pragma unroll
-                for (int p = 0; p < 32; ++p) sbias += (float)s_dz[wave][lane][p];
-                put<ONE>(&grad[kFieldOffB[L] + lane], sbias, first);
-            }
-            if (L >= 2) {
-                const unsigned char* Bm = s_blob + kOffB2 + (L - 2) * kMatH;
-                f32x16 e0 = {}, e1 = {};
-#pragma unroll
-                for (int ks = 0; ks < 4; ++ks) {
-                    e0 = mfma(lds8(Bm, n * kSH + 16 * ks + 8 * h), dzb[ks], e0);
-                    e1 = mfma(lds8(Bm, (32 + n) * kSH + 16 * ks + 8 * h), dzb[ks], e1);
-                }
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    dz0[v] = (float)A.h[L - 2][v >> 3][v & 7] > 0.0f ? e0[v] : 0.0f;
-                    dz1[v] = (float)A.h[L - 2][2 + (v >> 3)][v & 7] > 0.0f ? e1[v] : 0.0f;
-                }
+                dz0[v] = (float)A.h[L - 2][v >> 3][v & 7] > 0.0f ? e0[v] : 0.0f;
+                dz1[v] = (float)A.h[L - 2][2 + (v >> 3)][v & 7] > 0.0f ? e1[v] : 0.0f;
             }
         }
     }
 }
 
-// grad[net][p] = sum of the first `used` slots of network net; loss[net] likewise
-// (networks with no training points: cnt[net] == 0, nothing summed, 0).  A workgroup takes
-// kRedParams consecutive parameters of one network (blockIdx.y) and splits the slots into
-// kRedGroups contiguous runs, one per thread row; each row sums its run in slot order, then
-// one thread per parameter adds the rows in row order.  The order of every addition is fixed
-// by (used, slot), so the result is the same on every run.
-constexpr int kRedParams = 32;
-constexpr int kRedGroups = kThreads / kRedParams;
+// Row sums of the gradients over positions [q0, q0 + Q) of every row, continuing from
+// sums / part (the slot in progress) when q0 > 0: the two halves of layers 1..4's outputs in
+// blockIdx.z 0..7 (a wave per 32 of the layer's inputs), the biases and the output layer in 8
+// and 9.
+constexpr int kDwThreads = 192;
 
-__global__ void k_field_grad_reduce(const float* __restrict__ gpart, const double* __restrict__ lpart, int32_t used,
-                                    int32_t slots, const int64_t* __restrict__ cnt, float* __restrict__ grad,
-                                    double* __restrict__ loss)
+__global__ void __launch_bounds__(kDwThreads) k_field_dw(const unsigned char* __restrict__ buf, const int64_t* __restrict__ cnt,
+                                                         TileOrder ord, int q0, int Q, float* __restrict__ sums,
+                                                         float* __restrict__ part)
 {
-    __shared__ float rows[kRedGroups][kRedParams];
+    const int r = blockIdx.x, net = blockIdx.y, layer = blockIdx.z >> 1, mb = blockIdx.z & 1;
+    if (cnt && cnt[net] == 0) return;
+    const unsigned char* tiles = buf + ((int64_t)net * kRows + r) * Q * kTileBytes;
+    sums += ((int64_t)net * kRows + r) * kFieldParams;
+    part += ((int64_t)net * kRows + r) * kFieldParams;
+    const int lane = __lane_id(), wave = threadIdx.x >> 6;
+    // positions of this pass in the row, where a slot is one tile
+    const int m = max(0, min(Q, min(ord.used, (r + 1) * ord.per) - r * ord.per - q0));
+    if (layer == 4) {
+        const int p = mb * kDwThreads + threadIdx.x;
+        if (p >= kAux) return;
+        const int to = p < kW       ? kFieldOffB[1] + p
+                       : p < 4 * kW ? kFieldOffB[2] + (p / kW - 1) * (kFieldOffB[3] - kFieldOffB[2]) + p % kW
+                                    : kFieldOffW5 + p - 4 * kW;
+        float sum = q0 > 0 ? sums[to] : 0.0f, v = q0 > 0 ? part[to] : 0.0f;
+        const float* src = reinterpret_cast<const float*>(tiles + kOffAux) + p;
+        if (ord.rounds == 1) {
+            int q = 0;
+            for (; q + 16 <= m; q += 16) {  // sixteen loads in flight, added in slot order
+                float c[16];
+#pragma unroll
+                for (int k = 0; k < 16; ++k) c[k] = src[(int64_t)(q + k) * (kTileBytes / 4)];
+#pragma unroll
+                for (int k = 0; k < 16; ++k) sum += c[k];
+            }
+            for (; q < m; ++q) sum += src[(int64_t)q * (kTileBytes / 4)];
+            sums[to] = sum;
+            return;
+        }
+        for (int q = 0; q < Q; ++q) {
+            const int tile = tile_at(ord, r, q0 + q);
+            if (tile < 0) continue;
+            const float c = src[(int64_t)q * (kTileBytes / 4)];
+            v = (q0 + q) % ord.rounds == 0 ? c : v + c;
+            if (tile_at(ord, r, q0 + q + 1) < 0 || (q0 + q + 1) % ord.rounds == 0) sum += v;
+        }
+        sums[to] = sum;
+        part[to] = v;
+        return;
+    }
+    const int nk = layer == 0 ? 3 : 2;
+    const int nb = wave;
+    if (nb >= nk) return;
+    const int n = lane & 31, h = lane >> 5;
+    const int krow = layer == 0 ? input_feature(nb * 32 + n) : nb * 32 + n;
+    const int to = (layer == 0 ? kFieldOffW[1] : kFieldOffW[2] + (layer - 1) * (kFieldOffW[3] - kFieldOffW[2])) + krow * kW +
+                   mb * 32 + 4 * h;
+    const unsigned char* pa = tiles + kOffDz + layer * kDzBytes + mb * 2048 + 16 * lane;
+    const unsigned char* pb = tiles + (layer == 0 ? kOffX0 : kOffH + (layer - 1) * kDzBytes) + nb * 2048 + 16 * lane;
+    f32x16 sum = {}, v = {};
+    if (q0 > 0) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            sum[k] = sums[to + 8 * (k >> 2) + (k & 3)];
+            v[k] = part[to + 8 * (k >> 2) + (k & 3)];
+        }
+    }
+    if (ord.rounds == 1) {
+        // one tile a slot: the operands of the next eight tiles are in flight
+        constexpr int kAhead = 8;
+        bf16x8 a[kAhead][2], b[kAhead][2];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int64_t at = (int64_t)min(u, max(m - 1, 0)) * kTileBytes;
+#pragma unroll
+            for (int kp = 0; kp < 2; ++kp) {
+                a[u][kp] = *reinterpret_cast<const bf16x8*>(pa + at + 1024 * kp);
+                b[u][kp] = *reinterpret_cast<const bf16x8*>(pb + at + 1024 * kp);
+            }
+        }
+        for (int q = 0; q < m; q += kAhead) {
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                f32x16 c = {};
+                c = mfma(a[u][0], b[u][0], c);
+                c = mfma(a[u][1], b[u][1], c);
+                const int64_t at = (int64_t)min(q + u + kAhead, m - 1) * kTileBytes;
+#pragma unroll
+                for (int kp = 0; kp < 2; ++kp) {
+                    a[u][kp] = *reinterpret_cast<const bf16x8*>(pa + at + 1024 * kp);
+                    b[u][kp] = *reinterpret_cast<const bf16x8*>(pb + at + 1024 * kp);
+                }
+                if (q + u < m) {
+#pragma unroll
+                    for (int k = 0; k < 16; ++k) sum[k] += c[k];
+                }
+            }
+        }
+    } else {
+        for (int q = 0; q < Q; ++q) {
+            if (tile_at(ord, r, q0 + q) < 0) continue;
+            const int64_t at = (int64_t)q * kTileBytes;
+            f32x16 c = {};
+#pragma unroll
+            for (int kp = 0; kp < 2; ++kp)
+                c = mfma(*reinterpret_cast<const bf16x8*>(pa + at + 1024 * kp), *reinterpret_cast<const bf16x8*>(pb + at + 1024 * kp), c);
+            const bool first = (q0 + q) % ord.rounds == 0;
+            const bool last = (q0 + q + 1) % ord.rounds == 0 || tile_at(ord, r, q0 + q + 1) < 0;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                v[k] = first ? c[k] : v[k] + c[k];
+                if (last) sum[k] += v[k];
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        sums[to + 8 * (k >> 2) + (k & 3)] = sum[k];
+        if (ord.rounds > 1) part[to + 8 * (k >> 2) + (k & 3)] = v[k];
+    }
+}
+
+// the rows of a parameter in row order (networks with no training points: 0)
+__device__ __forceinline__ float row_total(const float* __restrict__ sums, int net, int p)
+{
+    const float* s = sums + (int64_t)net * kRows * kFieldParams + p;
+    float v[kRows];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) v[r] = s[(int64_t)r * kFieldParams];
+    float g = v[0];
+#pragma unroll
+    for (int r = 1; r < kRows; ++r) g += v[r];
+    return g;
+}
+
+// loss[net]: every slot the sum of its tiles in order, thread i of the workgroup the slots i,
+// i + kThreads, ... in order, then a fixed pairwise tree
+__device__ __forceinline__ void total_loss(const float* __restrict__ se, const TileOrder& ord, bool live, double* __restrict__ loss)
+{
     __shared__ double lrows[kThreads];
-    const int net = blockIdx.y;
-    const bool live = !cnt || cnt[net] > 0;
-    const int n = live ? used : 0;
-    const int col = threadIdx.x % kRedParams, row = threadIdx.x / kRedParams;
-    const int p = blockIdx.x * kRedParams + col;
-    const int per = (n + kRedGroups - 1) / kRedGroups;
-    const int w0 = row * per, w1 = min(n, w0 + per);
-    float sum = 0.0f;
-    if (p < kFieldParams) {
-        const float* src = gpart + (int64_t)net * slots * kFieldParams + p;
-        int w = w0;
-        for (; w + 8 <= w1; w += 8) {  // eight loads in flight, added in slot order
-            float v[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] = src[(int64_t)(w + k) * kFieldParams];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) sum += v[k];
-        }
-        for (; w < w1; ++w) sum += src[(int64_t)w * kFieldParams];
+    double l = 0.0;
+    for (int w = threadIdx.x; live && w < ord.used; w += kThreads) {
+        double v = (double)se[w];
+        for (int64_t tile = (int64_t)w + ord.slots; tile < ord.tiles; tile += ord.slots) v += (double)se[tile];
+        l += v;
     }
-    rows[row][col] = sum;
-    if (blockIdx.x == 0) {
-        // the loss: thread i sums slots i, i + kThreads, ... in order, then a fixed pairwise tree
-        double l = 0.0;
-        for (int w = threadIdx.x; w < n; w += kThreads) l += lpart[(int64_t)net * slots + w];
-        lrows[threadIdx.x] = l;
-    }
+    lrows[threadIdx.x] = l;
     __syncthreads();
-    if (row == 0 && p < kFieldParams) {
-        float s = rows[0][col];
-        for (int r = 1; r < kRedGroups; ++r) s += rows[r][col];
-        grad[(int64_t)net * kFieldParams + p] = s;
+    for (int h = kThreads / 2; h > 0; h >>= 1) {
+        if (threadIdx.x < h) lrows[threadIdx.x] += lrows[threadIdx.x + h];
+        __syncthreads();
     }
-    if (blockIdx.x == 0) {
-        for (int h = kThreads / 2; h > 0; h >>= 1) {
-            if (threadIdx.x < h) lrows[threadIdx.x] += lrows[threadIdx.x + h];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) loss[net] = lrows[0];
+    if (threadIdx.x == 0) *loss = lrows[0];
+}
+
+__global__ void __launch_bounds__(kThreads) k_field_grad(const float* __restrict__ sums, const float* __restrict__ se, TileOrder ord,
+                                                         float* __restrict__ grad, double* __restrict__ loss)
+{
+    const int p = blockIdx.x * kThreads + threadIdx.x;
+    if (p < kFieldParams) grad[p] = row_total(sums, 0, p);
+    if (blockIdx.x == 0) total_loss(se, ord, true, loss);
+}
+
+struct AdamStep {
+    float lr, b1, b2, eps, c1, c2;
+};
+
+__device__ __forceinline__ float adam(float& p, float& m, float& v, float g, const AdamStep& a)
+{
+    const float mi = a.b1 * m + (1.0f - a.b1) * g;
+    const float vi = a.b2 * v + (1.0f - a.b2) * g * g;
+    m = mi;
+    v = vi;
+    p -= a.lr * (mi * a.c1) / (sqrtf(vi * a.c2) + a.eps);
+    return p;
+}
+
+// where parameter p lies in the packed image: k_field_pack's inverse
+__device__ __forceinline__ void pack_param(unsigned char* blob, int p, float x)
+{
+    __bf16* bf = reinterpret_cast<__bf16*>(blob);
+    float* f32 = reinterpret_cast<float*>(blob);
+    // feature -> slot of a 16-wide step (slot_feature's inverse)
+    auto slot = [](int f) { return (f & 3) | ((f >> 3) << 2) | (((f >> 2) & 1) << 3); };
+    if (p < kFieldOffB[1]) {
+        const int k = p / kW, i = p % kW;  // feature index 6 band + 2 axis + (sin 0 | cos 1)
+        const int pr = k / 2;              // 3 band + axis = 8 (c / 16) + c % 8
+        bf[i * kS1 + 16 * (pr / 8) + 8 * (k & 1) + pr % 8] = (__bf16)x;
+        return;
     }
+    if (p >= kFieldOffW5) {
+        if (p < kFieldOffB5) f32[kOffW5 / 4 + p - kFieldOffW5] = x;
+        else f32[kOffB5 / 4] = x;
+        return;
+    }
+    if (p < kFieldOffW[2]) {
+        f32[kOffBias / 4 + p - kFieldOffB[1]] = x;
+        return;
+    }
+    const int L = (p - kFieldOffW[2]) / (kFieldOffW[3] - kFieldOffW[2]), o = p - kFieldOffW[2] - L * (kFieldOffW[3] - kFieldOffW[2]);
+    if (o >= kW * kW) {
+        f32[kOffBias / 4 + (L + 1) * kW + o - kW * kW] = x;
+        return;
+    }
+    const int k = o / kW, i = o % kW;
+    bf[kOffF2 / 2 + L * kW * kSH + i * kSH + 16 * (k / 16) + slot(k % 16)] = (__bf16)x;
+    bf[kOffB2 / 2 + L * kW * kSH + k * kSH + 16 * (i / 16) + slot(i % 16)] = (__bf16)x;
+}
+
+__global__ void __launch_bounds__(kThreads) k_field_step(const float* __restrict__ sums, const float* __restrict__ se,
+                                                         const int64_t* __restrict__ cnt, TileOrder ord, AdamStep a,
+                                                         float* __restrict__ master, float* __restrict__ m1,
+                                                         float* __restrict__ m2, unsigned char* __restrict__ blob,
+                                                         int64_t pack_stride, double* __restrict__ loss)
+{
+    const int net = blockIdx.y;
+    const bool live = cnt[net] > 0;
+    const int p = blockIdx.x * kThreads + threadIdx.x;
+    if (p < kFieldParams) {
+        const int64_t i = (int64_t)net * kFieldParams + p;
+        float x = master[i], m = m1[i], v = m2[i];
+        const float g = live ? row_total(sums, net, p) : 0.0f;
+        x = adam(x, m, v, g, a);
+        master[i] = x;
+        m1[i] = m;
+        m2[i] = v;
+        pack_param(blob + (int64_t)net * pack_stride, p, x);
+    }
+    if (blockIdx.x == 0) total_loss(se + (int64_t)net * ord.tiles, ord, live, loss + net);
 }
 
 __global__ void k_field_adam(float* __restrict__ p, float* __restrict__ m, float* __restrict__ v,
-                             float* __restrict__ grad, int64_t count, float lr, float b1, float b2, float eps,
-                             float c1, float c2)
+                             float* __restrict__ grad, int64_t count, AdamStep a)
 {
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (i >= count) return;
-    const float g = grad[i];
-    const float mi = b1 * m[i] + (1.0f - b1) * g;
-    const float vi = b2 * v[i] + (1.0f - b2) * g * g;
-    m[i] = mi;
-    v[i] = vi;
-    p[i] -= lr * (mi * c1) / (sqrtf(vi * c2) + eps);
+    (void)adam(p[i], m[i], v[i], grad[i], a);
     grad[i] = 0.0f;
 }
 
@@ -875,11 +1132,6 @@ inline unsigned blocks(int64_t n) { return (unsigned)((n + kThreads - 1) / kThre
 size_t field_pack_bytes() { return kPack; }
 size_t field_infer_bytes() { return kInfer; }
 
-void launch_field_pack(const float* master, unsigned char* blob, hipStream_t s)
-{
-    k_field_pack<<<blocks(kPackThreads), kThreads, 0, s>>>(master, blob, 0);
-}
-
 void launch_field_pack_nets(const float* master, unsigned char* blob, int32_t M, hipStream_t s)
 {
     if (M > 0) k_field_pack<<<dim3(blocks(kPackThreads), (unsigned)M), kThreads, 0, s>>>(master, blob, kPack);
@@ -926,50 +1178,86 @@ void launch_field_select(const uint32_t* flag, const int32_t* mesh, int32_t m, i
     if (n > 0) k_field_select<<<blocks(n), kThreads, 0, s>>>(flag, mesh, m, n, sel);
 }
 
-int32_t field_train_slots(int32_t batch, int32_t M)
+namespace {
+
+int64_t tiles_of(int32_t batch) { return ((int64_t)batch + 31) / 32; }
+
+// The slots of a step (they set the order of its sums): one per tile up to 4,096 and to 1 /
+// networks of 3,576 (a multiple of four, at least four).
+int32_t train_slots(int32_t batch, int32_t M)
 {
-    const int tiles = (batch + 31) / 32;
-    const int waves = kThreads / 64;
-    // at most ~256 MB of slots over all networks, at least one workgroup per network
+    const int64_t waves = kThreads / 64;
     const int64_t cap = std::max<int64_t>(1, ((int64_t)256 << 20) / ((int64_t)M * waves * kFieldParams * 4));
-    const int64_t grid = std::min<int64_t>(std::min<int64_t>((tiles + waves - 1) / waves, 1024), cap);
+    const int64_t grid = std::min<int64_t>(std::min<int64_t>((tiles_of(batch) + waves - 1) / waves, 1024), cap);
     return (int32_t)(std::max<int64_t>(grid, 1) * waves);
 }
 
-void launch_field_train(const unsigned char* blob, const FieldGeom& g, FieldTrain t, float* grad, double* loss,
-                        hipStream_t s)
+TileOrder tile_order(int32_t batch, int32_t M)
 {
-    if (t.batch <= 0) return;
-    const int tiles = (t.batch + 31) / 32;
-    t.slots = field_train_slots(t.batch, 1);
-    if (tiles <= t.slots)
-        k_field_train<true><<<(unsigned)(t.slots / (kThreads / 64)), kThreads, 0, s>>>(blob, g, t, FieldNets{});
-    else
-        k_field_train<false><<<(unsigned)(t.slots / (kThreads / 64)), kThreads, 0, s>>>(blob, g, t, FieldNets{});
-    k_field_grad_reduce<<<dim3((kFieldParams + kRedParams - 1) / kRedParams, 1), kThreads, 0, s>>>(
-        t.gpart, t.lpart, std::min(tiles, t.slots), t.slots, nullptr, grad, loss);
+    TileOrder o;
+    o.tiles = (int32_t)tiles_of(batch);
+    o.slots = train_slots(batch, M);
+    o.used = std::min(o.tiles, o.slots);
+    o.per = (o.used + kRows - 1) / kRows;
+    o.rounds = (o.tiles + o.slots - 1) / o.slots;
+    return o;
 }
 
-void launch_field_train_nets(const unsigned char* blob, const FieldNets& nets, int32_t M, FieldTrain t, float* grad,
-                             double* loss, hipStream_t s)
+// positions of a row that one pass of the two kernels takes: all of them up to 8,192 tiles
+// (285 MB) over the networks, else that many
+int32_t pass_positions(const TileOrder& o, int32_t M)
+{
+    const int64_t all = (int64_t)o.per * o.rounds;
+    return (int32_t)std::min<int64_t>(all, std::max<int64_t>(1, 8192 / ((int64_t)kRows * M)));
+}
+
+// row sums of one step over every network
+void launch_field_sums(const unsigned char* blob, const FieldGeom& g, const FieldTrain& t, const FieldNets& nets, int32_t M,
+                       const TileOrder& o, hipStream_t s)
+{
+    const int Q = pass_positions(o, M);
+    const int64_t all = (int64_t)o.per * o.rounds;
+    for (int64_t q0 = 0; q0 < all; q0 += Q) {
+        const dim3 grid((unsigned)((kRows * Q + kTileWaves - 1) / kTileWaves), (unsigned)M);
+        k_field_tiles<<<grid, 64 * kTileWaves, 0, s>>>(blob, g, t, nets, o, (int)q0, Q, t.buf);
+        k_field_dw<<<dim3(kRows, (unsigned)M, 10), kDwThreads, 0, s>>>(t.buf, nets.cnt, o, (int)q0, Q, t.sums, t.part);
+    }
+}
+
+}  // namespace
+
+void field_train_bytes(int32_t batch, int32_t M, size_t& buf, size_t& sums, size_t& se)
+{
+    const TileOrder o = tile_order(batch, M);
+    buf = (size_t)M * kRows * (size_t)pass_positions(o, M) * kTileBytes;
+    sums = (size_t)M * kRows * kFieldParams * sizeof(float);
+    se = (size_t)M * (size_t)o.tiles * sizeof(float);
+}
+
+void launch_field_gradient(const unsigned char* blob, const FieldGeom& g, const FieldTrain& t, float* grad, double* loss,
+                           hipStream_t s)
+{
+    if (t.batch <= 0) return;
+    const TileOrder o = tile_order(t.batch, 1);
+    launch_field_sums(blob, g, t, FieldNets{}, 1, o, s);
+    k_field_grad<<<blocks(kFieldParams), kThreads, 0, s>>>(t.sums, t.se, o, grad, loss);
+}
+
+void launch_field_step(unsigned char* blob, const FieldNets& nets, int32_t M, const FieldTrain& t, float* master, float* m,
+                       float* v, float lr, float b1, float b2, float eps, float c1, float c2, double* loss, hipStream_t s)
 {
     if (t.batch <= 0 || M <= 0) return;
-    const int tiles = (t.batch + 31) / 32;
-    t.slots = field_train_slots(t.batch, M);
-    const dim3 grid((unsigned)(t.slots / (kThreads / 64)), (unsigned)M);
-    if (tiles <= t.slots)
-        k_field_train<true><<<grid, kThreads, 0, s>>>(blob, FieldGeom{}, t, nets);
-    else
-        k_field_train<false><<<grid, kThreads, 0, s>>>(blob, FieldGeom{}, t, nets);
-    k_field_grad_reduce<<<dim3((kFieldParams + kRedParams - 1) / kRedParams, (unsigned)M), kThreads, 0, s>>>(
-        t.gpart, t.lpart, std::min(tiles, t.slots), t.slots, nets.cnt, grad, loss);
+    const TileOrder o = tile_order(t.batch, M);
+    launch_field_sums(blob, FieldGeom{}, t, nets, M, o, s);
+    k_field_step<<<dim3(blocks(kFieldParams), (unsigned)M), kThreads, 0, s>>>(t.sums, t.se, nets.cnt, o, AdamStep{lr, b1, b2, eps, c1, c2},
+                                                                            master, m, v, blob, nets.pack_stride, loss);
 }
 
 void launch_field_adam(float* master, float* m, float* v, float* grad, int64_t count, float lr, float b1, float b2,
                        float eps, float c1, float c2, hipStream_t s)
 {
     if (count > 0)
-        k_field_adam<<<blocks(count), kThreads, 0, s>>>(master, m, v, grad, count, lr, b1, b2, eps, c1, c2);
+        k_field_adam<<<blocks(count), kThreads, 0, s>>>(master, m, v, grad, count, AdamStep{lr, b1, b2, eps, c1, c2});
 }
 
 void launch_field_split(int64_t n, uint32_t key0, uint32_t key1, uint32_t threshold, uint32_t* flag, hipStream_t s)
