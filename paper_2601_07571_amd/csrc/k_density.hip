@@ -1039,6 +1039,81 @@ __global__ void __launch_bounds__(256) k_horizon(const float4* __restrict__ spos
     if (i < n) hz[i] = h;
 }
 
+// The same for few points, a wave each: a packet of few points is one long chain of dependent
+// node loads with most lanes idle.  Here a round takes up to 32 nodes off the wave's stack, a
+// lane for each child, and the triangles of the leaves it opens, a lane for each; the bound of
+// all lanes is shared after the leaves of a round.
+constexpr int kHzStack = 512;
+constexpr int kHzRound = 32;
+
+__global__ void __launch_bounds__(256) k_horizon_wide(const float4* __restrict__ spos, const float4* __restrict__ bface,
+                                                      int64_t n, const BvhNode* __restrict__ nodes,
+                                                      const BvhTri* __restrict__ tris, float reach,
+                                                      float* __restrict__ hz)
+{
+    __shared__ int s_stack[4][kHzStack];
+    __shared__ int2 s_leaf[4][2 * kHzRound];
+    const int lane = lane_id();
+    const int wave = (int)(threadIdx.x >> 6);
+    const int64_t i = (int64_t)blockIdx.x * 4 + wave;
+    if (i >= n) return;
+    // written and read by this wave alone, whose LDS operations complete in order
+    volatile int* stack = s_stack[wave];
+    volatile int* leaves = reinterpret_cast<volatile int*>(s_leaf[wave]);
+    const float4 p = spos[i], b = bface[i];
+    const int t = __float_as_int(p.w);
+    const float reach2 = reach * reach * 1.001f;
+    const float n2 = __builtin_fmaf(b.x, b.x, __builtin_fmaf(b.y, b.y, b.z * b.z));
+    const bool on = t >= 0 && n2 >= 1e-30f;
+    const float inv = on ? rsqrtf(n2) : 0.0f;
+    HzPoint P = hz_point(p.x, p.y, p.z, b.x * inv, b.y * inv, b.z * inv, kHzFloor);
+    int sp = uniform(on ? 1 : 0), visits = 0;
+    bool whole = true;
+    if (lane == 0) stack[0] = 0;
+    while (sp > 0) {
+        const int take = min(sp, kHzRound);
+        visits += take;
+        sp -= take;
+        if (visits > kHzVisits) {
+            whole = false;
+            break;
+        }
+        const bool mine = (lane >> 1) < take;
+        const int c = lane & 1;
+        const float* nd = reinterpret_cast<const float*>(nodes + (mine ? stack[sp + (lane >> 1)] : 0));
+        const float lo[3] = {nd[6 * c], nd[6 * c + 1], nd[6 * c + 2]};
+        const float hi[3] = {nd[6 * c + 3], nd[6 * c + 4], nd[6 * c + 5]};
+        const int child = __float_as_int(nd[12 + c]), count = __float_as_int(nd[14 + c]) & kCountMask;
+        float s;
+        const bool open = hz_box(P, lo, hi, reach2, s) && mine;
+        const uint64_t below = (1ull << lane) - 1;
+        const uint64_t inner = ballot(open && child >= 0), leaf = ballot(open && child < 0);
+        if (sp + (int)__popcll(inner) > kHzStack) {
+            whole = false;
+            break;
+        }
+        if (open && child >= 0) stack[sp + (int)__popcll(inner & below)] = child;
+        sp += (int)__popcll(inner);
+        if (leaf == 0) continue;
+        if (open && child < 0) {
+            const int j = (int)__popcll(leaf & below);
+            leaves[2 * j] = ~child;
+            leaves[2 * j + 1] = count;
+        }
+        const int slots = (int)__popcll(leaf) * kLeafMax;
+        for (int q = lane; q < slots; q += 64) {
+            const int j = q / kLeafMax, k = q % kLeafMax;
+            if (k >= leaves[2 * j + 1]) continue;
+            const BvhTri tr = load_tri_v(tris, leaves[2 * j] + k);
+            if (tr.id != t) hz_tri(P, tr);
+        }
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) P.H = fmaxf(P.H, __shfl_xor(P.H, d, 64));
+        if (uniform(P.H >= kHzCap ? 1 : 0)) break;  // nothing left to find
+    }
+    if (lane == 0) hz[i] = on && whole ? hz_sin2(P.H) : kHzNever;
+}
+
 // What the rules say of point i (sorted order) and eye e: true when the pair is occluded by
 // the point's own closed mesh; else t0 is where the walk of its segment may begin (beyond the
 // part that the horizon clears, else kTlo; 1: all of it is clear).
@@ -2402,10 +2477,19 @@ void launch_backface_prep(const float4* spos, const int32_t* smesh, int64_t n, c
     }
 }
 
+// Points that take a wave each (k_horizon_wide) rather than share packets: the packets' time is
+// the length of one walk until they fill the chip and then grows slowly, the wide kernel's grows
+// with the points.  Preparation of a map with either, wide / packets, at 12,007 points 113 / 344
+// us (a sphere of 60,000 triangles) and 119 / 433 (objects of 200,000); 120,000 468 / 613 and 503 /
+// 951; 250,000 861 / 676 and 914 / 1,199; 500,000 1,601 / 723 and 1,605 / 1,191.
+constexpr int64_t kHzWide = 163840;
+
 void launch_horizon(const float4* spos, const float4* bface, int64_t n, const BvhNode* nodes, const BvhTri* tris,
                     float reach, float* hz, hipStream_t s)
 {
-    if (n > 0) {
+    if (n > 0 && n <= kHzWide) {
+        k_horizon_wide<<<blocks(n, 4), 256, 0, s>>>(spos, bface, n, nodes, tris, reach, hz);
+    } else if (n > 0) {
         const int lg = prep_lanes_log2(n);
         const int64_t waves = (n + (int64_t(1) << lg) - 1) >> lg;
         k_horizon<<<blocks(waves * 64, 256), 256, 0, s>>>(spos, bface, n, nodes, tris, reach, lg, hz);
