@@ -362,14 +362,18 @@ gm_status density_backface(gm_scene* sc, DensityWork& w, int64_t n, uint32_t mod
     return GM_OK;
 }
 
-bool horizon_pays(int64_t F, double sigma, uint32_t mode)
+bool horizon_pays(int64_t n, int64_t F, double sigma, uint32_t mode)
 {
     // A point's walked pairs grow with F sigma^2 (its share of the cones), its horizon costs
     // one walk of its neighbourhood.  Map time without / with: three objects and a terrain,
     // 300,021 points, 2,500 fixations at 1 degree (F sigma^2 = 0.76) 3.68 / 3.97 ms; a sphere,
     // 12,007 points, 2,501 at 1.2 degrees (1.1) 1.13 / 1.01; 2M points, 6,000 at 1 degree (1.8)
     // 34.0 / 29.5; 25 spheres, 400,003 points, 12,000 (3.7) 15.4 / 14.3.
-    return mode != GM_OCC_NONE && (double)F * sigma * sigma >= 1.0;
+    // Few points, a wave each, have theirs for 40 to 150 us: a sphere, 30,000 points, 300 / 600 /
+    // 1,200 / 2,400 fixations at 1 degree (0.09 / 0.18 / 0.37 / 0.73) 509 / 551 / 784 / 1,244 us
+    // without, 469 / 543 / 661 / 901 with; 25 spheres 520 / 714 / 832 / 1,122 and 568 / 593 /
+    // 735 / 1,033; 120,000 points at 0.37 / 0.73 1,249 / 1,909 and 1,420 / 1,989.
+    return mode != GM_OCC_NONE && (double)F * sigma * sigma >= (n <= 65536 ? 0.2 : 1.0);
 }
 
 gm_status density_horizon(gm_scene* sc, DensityWork& w, int64_t n, hipStream_t s)
@@ -396,7 +400,7 @@ gm_status density_prep(gm_scene* sc, DensityWork& w, const float* pos, const int
     launch_fix_prep(fix->eye, fix->gaze, fix->duration, F, sigma, kGateWiden, w.fix.as<FixRec>(), nullptr,
                     w.fx_shift.as<int32_t>(), s);
     density_sort(sc, w, pos, tri, mesh, n, s);
-    const bool horizon = horizon_pays(F, sigma, mode);
+    const bool horizon = horizon_pays(n, F, sigma, mode);
     w.horizon = false;
     gm_status st = density_backface(sc, w, n, mode, horizon, s);
     if (st == GM_OK && horizon) st = density_horizon(sc, w, n, s);

@@ -235,8 +235,8 @@ gm_status density_prep(gm_scene* sc, DensityWork& w, const float* pos, const int
 // (normals: also without a closed mesh, for the horizon rule)
 gm_status density_backface(gm_scene* sc, DensityWork& w, int64_t n, uint32_t mode, bool normals, hipStream_t s,
                            int64_t off = 0);
-// whether the points' horizons pay for themselves over F fixations
-bool horizon_pays(int64_t F, double sigma, uint32_t mode);
+// whether the horizons of n points pay for themselves over F fixations
+bool horizon_pays(int64_t n, int64_t F, double sigma, uint32_t mode);
 // the horizons of the n sorted points of w, whose normals density_backface has written
 gm_status density_horizon(gm_scene* sc, DensityWork& w, int64_t n, hipStream_t s);
 // squared length of the longest segment the rule takes (see DensityLaunch::bf_L2max)
