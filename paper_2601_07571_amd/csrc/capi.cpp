@@ -262,7 +262,7 @@ void density_sort(gm_scene* sc, DensityWork& w, const float* pos, const int32_t*
     const int cells = 1 << w.bits;
     const float inv_cell = ext > 0.0f ? (float)cells / ext : 1.0f;
     launch_morton(pos, tri, mesh, sc->tri_mesh.as<int32_t>(), n, lo, inv_cell, w.bits, w.key.as<uint32_t>(),
-                  w.hist.as<uint32_t>(), s);
+                  w.hist.as<uint32_t>(), w.inv.as<int32_t>() + off, s);
     launch_exclusive_scan_u32(w.hist.as<uint32_t>(), w.cursor.as<uint32_t>(), w.buckets, w.scan_tmp.p, s);
     launch_scatter(pos, tri, mesh, sc->tri_mesh.as<int32_t>(), sc->T, n, w.key.as<uint32_t>(),
                    w.cursor.as<uint32_t>(), w.spos.as<float4>() + off, w.smesh.as<int32_t>() + off,

@@ -113,6 +113,7 @@ void launch_lattice_sample(const float* V, const int32_t* I, const int32_t* tri_
                            float* bary, float* pos, hipStream_t s);
 
 // a2: inclusive prefix sum of uint64 over n (tmp: scan_tmp_bytes(n)).
+// The arrays and tmp are aligned to 16 bytes.
 size_t scan_tmp_bytes(int64_t n);
 void launch_inclusive_scan_u64(const unsigned long long* in, unsigned long long* out, int64_t n, void* tmp,
                                hipStream_t s);
@@ -249,10 +250,10 @@ void launch_fix_select(const float* eye, const float* gaze, const float* dur, co
                        unsigned long long* budget, unsigned long long* totals, hipStream_t s);
 void launch_morton(const float* pos, const int32_t* tri, const int32_t* mesh, const int32_t* tri_mesh,
                    int64_t n, const float* bbox_lo, float inv_cell, int bits, uint32_t* key, uint32_t* hist,
-                   hipStream_t s);
+                   int32_t* rank, hipStream_t s);  // rank[i]: point i's place in its bucket
 void launch_scatter(const float* pos, const int32_t* tri, const int32_t* mesh, const int32_t* tri_mesh,
-                    int64_t T, int64_t n, const uint32_t* key, uint32_t* cursor, float4* spos, int32_t* smesh,
-                    int32_t* inv, int32_t base, hipStream_t s);  // inv[i] = base + sorted position of point i
+                    int64_t T, int64_t n, const uint32_t* key, const uint32_t* first, float4* spos, int32_t* smesh,
+                    int32_t* inv, int32_t base, hipStream_t s);  // inv[i]: rank in, base + sorted position of point i out
 void launch_density(const DensityLaunch& a, hipStream_t s);
 // persistent multi-session form: items are (session, tile, chunk, 0); head is zeroed by the caller
 void launch_density_queue(const DensityLaunch* sessions, const int4* items, int32_t n_items, unsigned int* head,
