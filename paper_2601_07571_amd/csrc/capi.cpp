@@ -248,11 +248,13 @@ gm_status density_reserve(DensityWork& w, int64_t n, int32_t F)
 }
 
 void density_sort(gm_scene* sc, DensityWork& w, const float* pos, const int32_t* tri, const int32_t* mesh,
-                  int64_t n, hipStream_t s, int64_t off)
+                  int64_t n, hipStream_t s, int64_t off, bool zeroed)
 {
     if (n <= 0) return;
-    zero(w.acc.as<unsigned long long>() + off, 8 * (size_t)n, s);
-    zero(w.hist.p, 4 * (size_t)w.buckets, s);
+    if (!zeroed) {
+        zero(w.acc.as<unsigned long long>() + off, 8 * (size_t)n, s);
+        zero(w.hist.p, 4 * (size_t)w.buckets, s);
+    }
     float lo[3];
     float ext = 0.0f;
     for (int c = 0; c < 3; ++c) {
@@ -394,12 +396,21 @@ gm_status density_prep(gm_scene* sc, DensityWork& w, const float* pos, const int
 {
     const int32_t F = fix->n;
     const double sigma = std::tan(theta_deg * M_PI / 180.0);
-    zero(w.stats.p, 8 * kDensityStats, s);
-    zero(w.fx_shift.p, 16, s);
-    zero(w.max_acc.p, 8, s);
-    launch_fix_prep(fix->eye, fix->gaze, fix->duration, F, sigma, kGateWiden, w.fix.as<FixRec>(), nullptr,
-                    w.fx_shift.as<int32_t>(), s);
-    density_sort(sc, w, pos, tri, mesh, n, s);
+    MapBegin begin;
+    begin.eye = fix->eye;
+    begin.gaze = fix->gaze;
+    begin.dur = fix->duration;
+    begin.F = F;
+    begin.rec = w.fix.as<FixRec>();
+    begin.fx_shift = w.fx_shift.as<int32_t>();
+    begin.acc = w.acc.as<unsigned long long>();
+    begin.stats = w.stats.as<unsigned long long>();
+    begin.max_acc = w.max_acc.as<unsigned long long>();
+    begin.n = n;
+    begin.hist = w.hist.as<uint32_t>();
+    begin.buckets = w.buckets;
+    launch_map_begin(begin, sigma, kGateWiden, s);
+    density_sort(sc, w, pos, tri, mesh, n, s, 0, true);
     const bool horizon = horizon_pays(n, F, sigma, mode);
     w.horizon = false;
     gm_status st = density_backface(sc, w, n, mode, horizon, s);

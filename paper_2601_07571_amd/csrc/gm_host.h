@@ -245,7 +245,7 @@ float backface_l2max(const gm_scene* sc);
 // of the points into w (into entries [off, off + n), caller indices off + i); the
 // launch descriptor for F records in w.fix
 void density_sort(gm_scene* sc, DensityWork& w, const float* pos, const int32_t* tri, const int32_t* mesh,
-                  int64_t n, hipStream_t s, int64_t off = 0);
+                  int64_t n, hipStream_t s, int64_t off = 0, bool zeroed = false);
 void density_args(const gm_scene* sc, const DensityWork& w, int64_t n, int32_t F, double sigma, uint32_t mode,
                   int spl, int32_t fix_per_chunk, DensityLaunch& a);
 // fixations per work item for one launch (or one session of a batch) of `tiles` tiles and F

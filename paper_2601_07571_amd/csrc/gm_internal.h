@@ -112,6 +112,20 @@ void launch_lattice_sample(const float* V, const int32_t* I, const int32_t* tri_
                            const unsigned long long* C, int64_t T, int64_t N, double k, int32_t* tri, int32_t* mesh,
                            float* bary, float* pos, hipStream_t s);
 
+// What a map's preparation begins with, in one launch: zeroed accumulators, buckets (an even
+// number), counters and maximum, and the records and fixed-point scale of F fixations
+// (launch_fix_prep's).
+struct MapBegin {
+    const float *eye = nullptr, *gaze = nullptr, *dur = nullptr;
+    int32_t F = 0;
+    FixRec* rec = nullptr;
+    int32_t* fx_shift = nullptr;  // 16 bytes
+    unsigned long long *acc = nullptr, *stats = nullptr, *max_acc = nullptr;
+    int64_t n = 0;
+    uint32_t* hist = nullptr;
+    int64_t buckets = 0;
+};
+void launch_map_begin(const MapBegin& b, double sigma, double widen, hipStream_t s);
 // a2: inclusive prefix sum of uint64 over n (tmp: scan_tmp_bytes(n)).
 // The arrays and tmp are aligned to 16 bytes.
 size_t scan_tmp_bytes(int64_t n);

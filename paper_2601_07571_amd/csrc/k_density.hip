@@ -1347,16 +1347,59 @@ __global__ void k_fix_select(const float* __restrict__ eye, const float* __restr
     atomicAdd(&totals[0], 1ull);
 }
 
+__device__ __forceinline__ int fixed_shift(float wmax, int32_t F)
+{
+    int e = 0;
+    if (!(wmax > 0.0f)) return 0;
+    (void)frexp((double)F * (double)wmax, &e);
+    return 62 - e;
+}
+
 __global__ void k_fix_shift(const unsigned int* __restrict__ wmax_bits, int32_t F, int32_t* __restrict__ shift)
 {
-    const float wmax = __uint_as_float(*wmax_bits);
-    int e = 0;
-    if (wmax > 0.0f) {
-        (void)frexp((double)F * (double)wmax, &e);
-        *shift = 62 - e;
-    } else {
-        *shift = 0;
+    *shift = fixed_shift(__uint_as_float(*wmax_bits), F);
+}
+
+// What a map's preparation begins with: block 0 makes the fixation records and the scale (when
+// `fixations`; else it clears the scale's words), the others clear the buffers.  One launch
+// instead of five fills and two kernels: a map of 6,253 points x 100 fixations
+// 93 -> 85 us (with the scan of its buckets and its outputs in one launch each).
+// One block's records of 16,384 fixations take about as long as the fills of a launch that has
+// so many; more go to k_fix_prep.
+constexpr int kBeginThreads = 1024;
+constexpr int32_t kBeginFix = 16384;
+
+__global__ void __launch_bounds__(kBeginThreads) k_map_begin(MapBegin b, bool fixations, double inv_norm, double kappa_scale)
+{
+    if (blockIdx.x == 0) {
+        __shared__ float s_w[kBeginThreads / 64];
+        if (threadIdx.x < kDensityStats) b.stats[threadIdx.x] = 0ull;
+        float wmax = 0.0f;
+        for (int f = threadIdx.x; fixations && f < b.F; f += kBeginThreads) {
+            FixRec r;
+            (void)fix_record(b.eye, b.gaze, b.dur, f, inv_norm, kappa_scale, INFINITY, r);
+            b.rec[f] = r;
+            wmax = fmaxf(wmax, r.w);
+        }
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) wmax = fmaxf(wmax, __shfl_xor(wmax, d, 64));
+        if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = wmax;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int w = 1; w < kBeginThreads / 64; ++w) wmax = fmaxf(wmax, s_w[w]);
+            b.fx_shift[0] = fixed_shift(wmax, b.F);
+            b.fx_shift[1] = __float_as_int(wmax);
+            *b.max_acc = 0ull;
+        }
+        return;
     }
+    // 16 bytes a lane; an odd accumulator at the end by itself
+    const int64_t stride = (int64_t)(gridDim.x - 1) * kBeginThreads;
+    const int64_t first = (int64_t)(blockIdx.x - 1) * kBeginThreads + threadIdx.x;
+    const uint4 z = make_uint4(0, 0, 0, 0);
+    for (int64_t i = first; i < b.n / 2; i += stride) reinterpret_cast<uint4*>(b.acc)[i] = z;
+    for (int64_t i = first; i < b.buckets / 4; i += stride) reinterpret_cast<uint4*>(b.hist)[i] = z;
+    if (first == 0 && (b.n & 1)) b.acc[b.n - 1] = 0ull;
 }
 
 // Posed scenes.  pose [F][M][12]: row-major 3x4 (A | b) taking mesh m's own frame to
@@ -2233,6 +2276,38 @@ __global__ void k_finalize(const unsigned long long* __restrict__ acc, const int
     if (density_norm) density_norm[j] = mx ? (float)((double)v / (double)mx) : 0.0f;
 }
 
+// The same for few points: every block takes the maximum of all of them itself, which saves the
+// launch of k_max and its cleared word.
+constexpr int64_t kFinalizeOne = 16384;
+
+__global__ void __launch_bounds__(256) k_finalize_one(const unsigned long long* __restrict__ acc,
+                                                      const int32_t* __restrict__ inv, int64_t n,
+                                                      const int32_t* __restrict__ shift_p,
+                                                      unsigned long long* __restrict__ max_acc,
+                                                      float* __restrict__ density, float* __restrict__ density_norm,
+                                                      float* __restrict__ max_out)
+{
+    __shared__ unsigned long long s_m[4];
+    unsigned long long mx = 0;
+#pragma unroll 8
+    for (int64_t i = threadIdx.x; i < n; i += 256) mx = max(mx, acc[i]);
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) mx = max(mx, (unsigned long long)__shfl_xor(mx, d, 64));
+    if ((threadIdx.x & 63) == 0) s_m[threadIdx.x >> 6] = mx;
+    __syncthreads();
+    mx = max(max(s_m[0], s_m[1]), max(s_m[2], s_m[3]));
+    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int shift = *shift_p;
+    if (j == 0) {
+        *max_acc = mx;
+        if (max_out) *max_out = (float)ldexp((double)mx, -shift);
+    }
+    if (j >= n) return;
+    const unsigned long long v = acc[inv[j]];
+    if (density) density[j] = (float)ldexp((double)v, -shift);
+    if (density_norm) density_norm[j] = mx ? (float)((double)v / (double)mx) : 0.0f;
+}
+
 // ---------------------------------------------------------------------------
 // stage-isolated checks
 // ---------------------------------------------------------------------------
@@ -2330,6 +2405,17 @@ void launch_fix_prep(const float* eye, const float* gaze, const float* dur, int3
     unsigned int* wmax = reinterpret_cast<unsigned int*>(fx_shift + 1);
     if (F > 0) k_fix_prep<<<blocks(F, 256), 256, 0, s>>>(eye, gaze, dur, F, inv_norm, kappa_scale, rec, wmax);
     k_fix_shift<<<1, 1, 0, s>>>(wmax, F, fx_shift);
+}
+
+void launch_map_begin(const MapBegin& b, double sigma, double widen, hipStream_t s)
+{
+    const double inv_norm = 1.0 / (sigma * std::sqrt(2.0 * M_PI));
+    const double kappa_scale = (1.0 - widen) / (1.0 + 16.0 * sigma * sigma);
+    const int64_t words = std::max(b.n / 2, b.buckets / 4);
+    const unsigned fills = (unsigned)std::min<int64_t>((words + kBeginThreads - 1) / kBeginThreads + 1, 2048);
+    const bool fixations = b.F <= kBeginFix;
+    k_map_begin<<<1 + fills, kBeginThreads, 0, s>>>(b, fixations, inv_norm, kappa_scale);
+    if (!fixations) launch_fix_prep(b.eye, b.gaze, b.dur, b.F, sigma, widen, b.rec, nullptr, b.fx_shift, s);
 }
 
 void launch_zcam_prep(const float* eye, const float* gaze, const float* dur, const float* head, int32_t F,
@@ -2458,6 +2544,10 @@ int density_queue_grid(int spl, int fb)
 void launch_finalize(const unsigned long long* acc, const int32_t* inv, int64_t n, const int32_t* fx_shift,
                      unsigned long long* max_acc, float* density, float* density_norm, float* max_out, hipStream_t s)
 {
+    if (n > 0 && n <= kFinalizeOne) {
+        k_finalize_one<<<blocks(n, 256), 256, 0, s>>>(acc, inv, n, fx_shift, max_acc, density, density_norm, max_out);
+        return;
+    }
     if (n > 0) k_max<<<std::min<unsigned>(blocks(n, 256), 512u), 256, 0, s>>>(acc, n, max_acc);
     k_finalize<<<blocks(n > 0 ? n : 1, 256), 256, 0, s>>>(acc, inv, n, fx_shift, max_acc, density, density_norm,
                                                           max_out);

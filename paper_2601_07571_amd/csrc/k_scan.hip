@@ -49,7 +49,7 @@ __device__ __forceinline__ T block_exclusive(T v, T* total)
 // them are there (the arrays are aligned to 16 bytes): one element at a time, the scan of 2^24
 // buckets took 31 us for the totals and 64 us for the scan, 11 and 24 us this way.
 template <typename T>
-__device__ __forceinline__ void load_items(const T* __restrict__ in, int64_t base, int64_t n, T (&v)[kItems])
+__device__ __forceinline__ void load_items(const T* in, int64_t base, int64_t n, T (&v)[kItems])
 {
     if (base + kItems <= n) {
         uint4* q = reinterpret_cast<uint4*>(v);
@@ -61,58 +61,10 @@ __device__ __forceinline__ void load_items(const T* __restrict__ in, int64_t bas
     }
 }
 
-template <typename T>
-__global__ void __launch_bounds__(kThreads) k_block_totals(const T* __restrict__ in, int64_t n, T* __restrict__ totals)
+// the running sums of those elements from `run` on
+template <bool Inclusive, typename T>
+__device__ __forceinline__ void store_scan(T* out, int64_t base, int64_t n, T (&v)[kItems], T run)
 {
-    const int64_t base = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kItems;
-    alignas(16) T v[kItems];
-    load_items(in, base, n, v);
-    T s = 0;
-#pragma unroll
-    for (int i = 0; i < kItems; ++i) s += v[i];
-    T tot;
-    (void)block_exclusive(s, &tot);
-    if (threadIdx.x == 0) totals[blockIdx.x] = tot;
-}
-
-// One block scans the block totals (exclusive) with a running carry, kItems a thread at a time
-// (8,192 totals: 20 us by 256 threads, one each; 6 us this way).
-constexpr int kTotalsThreads = 1024;
-
-template <typename T>
-__global__ void __launch_bounds__(kTotalsThreads) k_scan_totals(T* __restrict__ totals, int64_t nb)
-{
-    T carry = 0;
-    for (int64_t b0 = 0; b0 < nb; b0 += kTotalsThreads * kItems) {
-        const int64_t base = b0 + (int64_t)threadIdx.x * kItems;
-        alignas(16) T v[kItems];
-        load_items<T>(totals, base, nb, v);
-        T s = 0;
-#pragma unroll
-        for (int i = 0; i < kItems; ++i) s += v[i];
-        T tot;
-        T run = carry + block_exclusive<kTotalsThreads>(s, &tot);
-#pragma unroll
-        for (int i = 0; i < kItems; ++i) {
-            if (base + i < nb) totals[base + i] = run;
-            run += v[i];
-        }
-        carry += tot;
-    }
-}
-
-template <typename T, bool Inclusive>
-__global__ void __launch_bounds__(kThreads) k_block_scan(const T* __restrict__ in, T* __restrict__ out, int64_t n,
-                                                         const T* __restrict__ offsets)
-{
-    const int64_t base = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kItems;
-    alignas(16) T v[kItems];
-    load_items(in, base, n, v);
-    T s = 0;
-#pragma unroll
-    for (int i = 0; i < kItems; ++i) s += v[i];
-    T tot;
-    T run = block_exclusive(s, &tot) + offsets[blockIdx.x];
 #pragma unroll
     for (int i = 0; i < kItems; ++i) {
         const T x = v[i];
@@ -130,14 +82,71 @@ __global__ void __launch_bounds__(kThreads) k_block_scan(const T* __restrict__ i
     }
 }
 
+template <typename T>
+__global__ void __launch_bounds__(kThreads) k_block_totals(const T* __restrict__ in, int64_t n, T* __restrict__ totals)
+{
+    const int64_t base = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kItems;
+    alignas(16) T v[kItems];
+    load_items(in, base, n, v);
+    T s = 0;
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) s += v[i];
+    T tot;
+    (void)block_exclusive(s, &tot);
+    if (threadIdx.x == 0) totals[blockIdx.x] = tot;
+}
+
+// One block scans n elements (out may be in) with a running carry, kItems a thread at a time
+// (8,192 totals: 20 us by 256 threads, one each; 5 us this way).
+constexpr int kOneThreads = 1024;
+
+template <typename T, bool Inclusive>
+__global__ void __launch_bounds__(kOneThreads) k_scan_one(const T* in, T* out, int64_t n)
+{
+    T carry = 0;
+    for (int64_t b0 = 0; b0 < n; b0 += kOneThreads * kItems) {
+        const int64_t base = b0 + (int64_t)threadIdx.x * kItems;
+        alignas(16) T v[kItems];
+        load_items(in, base, n, v);
+        T s = 0;
+#pragma unroll
+        for (int i = 0; i < kItems; ++i) s += v[i];
+        T tot;
+        T run = carry + block_exclusive<kOneThreads>(s, &tot);
+        store_scan<Inclusive>(out, base, n, v, run);
+        carry += tot;
+    }
+}
+
+template <typename T, bool Inclusive>
+__global__ void __launch_bounds__(kThreads) k_block_scan(const T* __restrict__ in, T* __restrict__ out, int64_t n,
+                                                         const T* __restrict__ offsets)
+{
+    const int64_t base = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kItems;
+    alignas(16) T v[kItems];
+    load_items(in, base, n, v);
+    T s = 0;
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) s += v[i];
+    T tot;
+    T run = block_exclusive(s, &tot) + offsets[blockIdx.x];
+    store_scan<Inclusive>(out, base, n, v, run);
+}
+
 template <typename T, bool Inclusive>
 void scan(const T* in, T* out, int64_t n, void* tmp, hipStream_t s)
 {
     if (n <= 0) return;
+    // one launch where one block takes no longer than three (32,768 elements: 7.4 us; 8 us and
+    // two more launches otherwise)
+    if (n <= 4 * kOneThreads * kItems) {
+        k_scan_one<T, Inclusive><<<1, kOneThreads, 0, s>>>(in, out, n);
+        return;
+    }
     const int64_t nb = (n + kTile - 1) / kTile;
     T* totals = static_cast<T*>(tmp);
     k_block_totals<T><<<(unsigned)nb, kThreads, 0, s>>>(in, n, totals);
-    k_scan_totals<T><<<1, kTotalsThreads, 0, s>>>(totals, nb);
+    k_scan_one<T, false><<<1, kOneThreads, 0, s>>>(totals, totals, nb);
     k_block_scan<T, Inclusive><<<(unsigned)nb, kThreads, 0, s>>>(in, out, n, totals);
 }
 
