@@ -286,11 +286,13 @@ int32_t auto_fix_per_chunk(int64_t tiles, int32_t F, double tile_fixations, uint
     // 100 / 110 / 132 / 153 / 196 / 252 us; 47 x 2,501 1.17 / 1.11 / 1.17 / 1.22 / 1.43 /
     // 1.97 ms; 196 x 1,000 1.32 / 1.25 / 1.34 / 1.68 / 2.05 / 3.25 ms; 1,173 x 3,000 6.8 /
     // 5.2 / 4.2 / 3.7 / 3.7 / 4.4 ms; 1,563 x 12,000 38.9 / 29.7 / 24.2 / 21.1 / 19.7 / 19.4
-    // ms.  Without: 40 x 1,000 157 / 110 / 82 / 78 / 92 / 132 us; 391 x 3,000 2.17 / 1.48 /
-    // 0.93 / 0.56 / 0.33 / 0.27 ms (0.32 at 256, 0.46 at 512).
+    // ms.  The smallest, at 1 / 2 / 4 / 8: 25 x 100 82 / 80 / 88 / 91 us; 47 x 100 on a fine mesh
+    // (60,000 triangles) 242 / 275 / 364 / 382; 59 x 100 in a room 250 / 256 / 316 / 379; 196 x
+    // 100 340 / 352 / 417 / 421.  Without: 40 x 1,000 157 / 110 / 82 / 78 / 92 / 132 us; 391 x
+    // 3,000 2.17 / 1.48 / 0.93 / 0.56 / 0.33 / 0.27 ms (0.32 at 256, 0.46 at 512).
     const bool occ = mode != GM_OCC_NONE;
     const double root = std::sqrt(std::max(1.0, tile_fixations));
-    const int64_t min_chunk = std::min<int64_t>(occ ? 128 : 512, std::max<int64_t>(occ ? 4 : 16, (int64_t)(root / (occ ? 40.0 : 8.0))));
+    const int64_t min_chunk = std::min<int64_t>(occ ? 128 : 512, std::max<int64_t>(occ ? 1 : 16, (int64_t)(root / (occ ? 40.0 : 8.0))));
     const int64_t max_chunks = std::max<int64_t>(1, (F + min_chunk - 1) / min_chunk);
     const int64_t want = std::max<int64_t>((524288 + tiles - 1) / tiles, (F + 1023) / 1024);
     // the grid is tiles x chunks: chunks <= 65535 (grid y) and tiles x chunks < 2^31
