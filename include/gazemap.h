@@ -573,8 +573,9 @@ gm_status gm_batch_destroy(gm_batch* batch);
 /*
  * gm_density_stats: counters of the last accumulate_density call on this scene,
  * host int64 out[4] = {pairs inside the 4-sigma cone, of those visible, packet
- * traversals of the BVH (one per wave, fixation and sample slot with at least one
- * in-cone lane), BVH node visits}.  Blocking (synchronises the device).
+ * traversals (one per wave, fixation and sample slot with at least one lane that no rule
+ * has settled), node visits of the BVH and of the tree of boxes inside closed meshes}.
+ * Blocking (synchronises the device).
  */
 gm_status gm_density_stats(gm_scene* scene, int64_t* out);
 

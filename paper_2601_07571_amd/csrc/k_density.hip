@@ -2206,8 +2206,8 @@ __device__ __forceinline__ void density_item(const DensityLaunch& a, int64_t til
 // k_zbuffer) ask for 8 waves per SIMD, the most the SIMD holds; their scalar registers
 // then no longer fit and the compiler moves some long-lived ones (kernel arguments,
 // mostly outside the walk) into vector-register lanes.  More waves hide more of the
-// dependent node loads: the paper-shaped map takes 70.7 ms this way against 78.2 ms at
-// the 7 waves the register counts allow otherwise.
+// dependent node loads: without the rules that settle pairs beforehand, the paper-shaped map
+// takes 70.7 ms this way against 78.2 ms at the 7 waves the register counts allow otherwise.
 template <int SPL, int OCC>
 constexpr int kMinWaves = (SPL == 1 && OCC != 0) ? 8 : 1;
 
