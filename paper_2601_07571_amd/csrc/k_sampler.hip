@@ -129,6 +129,31 @@ __global__ void k_sample_guide(const unsigned long long* __restrict__ C, const i
     guide[e] = (int32_t)l;
 }
 
+// index of a wave's first item, in a scalar register
+__device__ __forceinline__ int64_t wave_first(int64_t i)
+{
+    const uint64_t w = (uint64_t)(i - (int64_t)(threadIdx.x & 63));
+    return (int64_t)(((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(w >> 32)) << 32) |
+                     __builtin_amdgcn_readfirstlane((uint32_t)w));
+}
+
+// what the samples of one mesh share
+struct MeshRange {
+    int64_t first;                     // its first sample
+    unsigned long long total, before;  // its weight, and all before it
+    int64_t guide;
+    int32_t shift;
+};
+
+__device__ __forceinline__ MeshRange mesh_range(int32_t m, const unsigned long long* __restrict__ C,
+                                                const int64_t* __restrict__ tri_off, const int64_t* __restrict__ offsets,
+                                                const unsigned long long* __restrict__ mesh_total,
+                                                const int64_t* __restrict__ goff, const int32_t* __restrict__ gsh)
+{
+    const int64_t a = tri_off[m];
+    return MeshRange{offsets[m], mesh_total[m], a > 0 ? C[a - 1] : 0ull, goff[m], gsh[m]};
+}
+
 __global__ void __launch_bounds__(kBlock)
 k_sample(const float* __restrict__ V, const int32_t* __restrict__ I, const unsigned long long* __restrict__ C,
          const int64_t* __restrict__ tri_off, const int64_t* __restrict__ offsets,
@@ -140,23 +165,37 @@ k_sample(const float* __restrict__ V, const int32_t* __restrict__ I, const unsig
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= N) return;
     // mesh of sample i: last m with offsets[m] <= i (offsets is non-decreasing)
-    int32_t lo = 0, hi = M - 1;
-    while (lo < hi) {
-        const int32_t mid = (lo + hi + 1) >> 1;
-        if (offsets[mid] <= i) lo = mid; else hi = mid - 1;
+    auto mesh_of = [&](int64_t q) {
+        int32_t lo = 0, hi = M - 1;
+        while (lo < hi) {
+            const int32_t mid = (lo + hi + 1) >> 1;
+            if (offsets[mid] <= q) lo = mid; else hi = mid - 1;
+        }
+        return lo;
+    };
+    // The kernel is bound by the vector memory path (its return side is busy 98 % of the time,
+    // mostly with the scattered reads of guide, weights, indices and vertices): nearly every wave
+    // lies in one mesh, whose numbers it reads once, by scalar loads (2,000,010 samples on four
+    // meshes of 200,000 triangles 45.7 -> 44.7 us).
+    const int64_t w0 = wave_first(i);
+    MeshRange r;
+    int32_t m = mesh_of(w0);
+    if (m == mesh_of(min(w0 + 63, N - 1))) {
+        r = mesh_range(m, C, tri_off, offsets, mesh_total, goff, gsh);
+    } else {
+        m = mesh_of(i);
+        r = mesh_range(m, C, tri_off, offsets, mesh_total, goff, gsh);
     }
-    const int32_t m = lo;
-    const uint64_t j = (uint64_t)(i - offsets[m]);
+    const uint64_t j = (uint64_t)(i - r.first);
     uint32_t x0 = (uint32_t)j, x1 = (uint32_t)(j >> 32), x2 = (uint32_t)m, x3 = 0u;
     philox4x32_10(x0, x1, x2, x3, key0, key1);
 
     // area-weighted triangle: the first with inclusive weight sum above the target
     const uint64_t U = ((uint64_t)x0 << 32) | (uint64_t)x1;
-    const uint64_t target = __umul64hi(U, mesh_total[m]);
-    const int64_t a = tri_off[m];
-    const uint64_t goal = (a > 0 ? C[a - 1] : 0ull) + target;
+    const uint64_t target = __umul64hi(U, r.total);
+    const uint64_t goal = r.before + target;
     // the guide bucket bounds the search (usually to one or two triangles)
-    const int64_t gk = goff[m] + (int64_t)(target >> gsh[m]);
+    const int64_t gk = r.guide + (int64_t)(target >> r.shift);
     int64_t l = guide[gk], h = guide[gk + 1];
     while (l < h) {
         const int64_t mid = l + ((h - l) >> 1);
@@ -239,13 +278,18 @@ k_lattice_sample(const float* __restrict__ V, const int32_t* __restrict__ I, con
 {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= N) return;
-    // triangle: the first with inclusive point count above i
-    int64_t l = 0, h = T - 1;
-    while (l < h) {
-        const int64_t mid = l + ((h - l) >> 1);
-        if (C[mid] > (unsigned long long)i) h = mid; else l = mid + 1;
-    }
-    const int64_t t = l;
+    // triangle: the first with inclusive point count above i; first that of the wave's first
+    // point, by scalar loads (every triangle holds points: the wave's lie in the next 64); a
+    // lattice call of 1,000,003 points on 200,000 triangles 56.1 -> 55.4 us
+    auto search = [&](int64_t l, int64_t h, int64_t q) {
+        while (l < h) {
+            const int64_t mid = l + ((h - l) >> 1);
+            if (C[mid] > (unsigned long long)q) h = mid; else l = mid + 1;
+        }
+        return l;
+    };
+    const int64_t tw = search(0, T - 1, wave_first(i));
+    const int64_t t = search(tw, min(tw + 63, T - 1), i);
     const int64_t idx = i - (t > 0 ? (int64_t)C[t - 1] : 0);
     const int64_t r = lattice_resolution(k, area[t]);
     int64_t row = (int64_t)ceil((sqrt(8.0 * (double)idx + 9.0) - 3.0) / 2.0);
