@@ -366,6 +366,18 @@ gm_status density_backface(gm_scene* sc, DensityWork& w, int64_t n, uint32_t mod
     return GM_OK;
 }
 
+bool horizon_room(DensityWork& w, int64_t n, hipStream_t s)
+{
+    const size_t bf = 16 * (size_t)n, bc = 4 * (size_t)kBfCand * (size_t)n, hz = 4 * (size_t)n;
+    if (w.bface.bytes >= bf && w.bcand.bytes >= bc && w.hz.bytes >= hz) return true;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusActive;
+    if (hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusNone &&
+        w.bface.ensure(bf) == hipSuccess && w.bcand.ensure(bc) == hipSuccess && w.hz.ensure(hz) == hipSuccess)
+        return true;
+    (void)hipGetLastError();
+    return false;
+}
+
 bool horizon_pays(int64_t n, int64_t F, double sigma, uint32_t mode)
 {
     // A point's walked pairs grow with F sigma^2 (its share of the cones), its horizon costs
@@ -413,7 +425,7 @@ gm_status density_prep(gm_scene* sc, DensityWork& w, const float* pos, const int
     begin.buckets = w.buckets;
     launch_map_begin(begin, sigma, kGateWiden, s);
     density_sort(sc, w, pos, tri, mesh, n, s, 0, true);
-    const bool horizon = horizon_pays(n, F, sigma, mode);
+    const bool horizon = n > 0 && horizon_pays(n, F, sigma, mode) && horizon_room(w, n, s);
     w.horizon = false;
     gm_status st = density_backface(sc, w, n, mode, horizon, s);
     if (st == GM_OK && horizon) st = density_horizon(sc, w, n, s);

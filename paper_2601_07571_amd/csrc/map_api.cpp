@@ -145,7 +145,7 @@ gm_status map_horizon(gm_map* m, int64_t F, hipStream_t s)
         GM_HIP(hipStreamWaitEvent(s, m->horizon, 0));
         return GM_OK;
     }
-    if (m->n <= 0 || !horizon_pays(m->n, F, m->sigma, m->mode)) return GM_OK;
+    if (m->n <= 0 || !horizon_pays(m->n, F, m->sigma, m->mode) || !horizon_room(m->w, m->n, s)) return GM_OK;
     gm_status st = GM_OK;
     if (!m->w.backface) st = density_backface(m->scene, m->w, m->n, m->mode, true, s);
     if (st == GM_OK && !m->horizon) GM_HIP(hipEventCreateWithFlags(&m->horizon, hipEventDisableTiming));
