@@ -159,7 +159,8 @@ struct gm_scene {
     // where the per-density counts follow without a device round trip); counts and
     // offsets are rewritten by each sampling call; lat_* hold the lattice sampler's
     // per-triangle counts and their scan
-    DevBuf area, W, C, max_bits, S, scan_tmp, counts, offsets, mesh_total, lat_W, lat_C;
+    DevBuf area, W, C, max_bits, S, scan_tmp, counts, offsets, mesh_total, lat_C;
+    int64_t* lat_totals = nullptr;  // the lattice sampler's per-mesh counts (pinned host memory)
     // the sampler's guide table (built with the weights): per mesh m, buckets of equal
     // width 2^gsh[m] in its target range, guide[goff[m] + k] = the triangle that the
     // bucket's lowest target selects, and one closing entry per mesh
@@ -212,6 +213,7 @@ struct gm_scene {
     ~gm_scene()
     {
         for (auto& t : timers) t.release();
+        if (lat_totals) (void)hipHostFree(lat_totals);
         for (DevBuf* b : {&V, &I, &tri_mesh, &tri_off_d, &nodes, &tris, &area, &W, &C, &max_bits, &S, &scan_tmp,
                           &counts, &offsets, &mesh_total, &blas_nodes, &blas_tris, &blas_desc})
             b->release();

@@ -103,9 +103,9 @@ void launch_mesh_scale(const unsigned long long* max_bits, const int64_t* tri_of
 // a1: fixed-point weights W_i = floor(A_i 2^S_m).
 void launch_tri_weight(const double* area, const int32_t* tri_mesh, const int32_t* S, int64_t T,
                        unsigned long long* W, hipStream_t s);
-// Lattice sampler: per-triangle point counts from the areas, per-mesh totals from
-// their inclusive scan C, and the points themselves.
-void launch_lattice_count(const double* area, int64_t T, double k, unsigned long long* cnt, hipStream_t s);
+// Lattice sampler: the inclusive scan of the triangles' point counts, formed from their areas
+// (tmp as for the scans below), per-mesh totals from it, and the points themselves.
+void launch_lattice_scan(const double* area, double k, unsigned long long* out, int64_t n, void* tmp, hipStream_t s);
 void launch_lattice_mesh_counts(const unsigned long long* C, const int64_t* tri_off, int32_t M, int64_t* counts,
                                 hipStream_t s);
 void launch_lattice_sample(const float* V, const int32_t* I, const int32_t* tri_mesh, const double* area,

@@ -8,6 +8,7 @@
 #include <algorithm>
 
 #include "gm_internal.h"
+#include "gm_lattice.h"
 #include "gm_philox.h"
 
 namespace gm {
@@ -233,27 +234,6 @@ k_sample(const float* __restrict__ V, const int32_t* __restrict__ I, const unsig
 // at resolution r_t holds (r_t + 1)(r_t + 2) / 2 points (Eq. 1) whose
 // barycentrics are multiples of 1 / r_t, indexed row by row.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int64_t lattice_points(int64_t r) { return (r + 1) * (r + 2) / 2; }
-
-// Eq. (4): Delta = (8 k) A + 1; r = 1 below Delta = 25, else the positive root
-// (sqrt(Delta) - 3) / 2 truncated to a whole resolution.
-__device__ __forceinline__ int64_t lattice_resolution(double k, double A)
-{
-    double delta = 8.0 * k;
-    delta = delta * A;
-    delta = delta + 1.0;
-    if (!(delta >= 25.0)) return 1;
-    return (int64_t)floor((sqrt(delta) - 3.0) / 2.0);
-}
-
-__global__ void k_lattice_count(const double* __restrict__ area, int64_t T, double k,
-                                unsigned long long* __restrict__ cnt)
-{
-    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (t >= T) return;
-    cnt[t] = (unsigned long long)lattice_points(lattice_resolution(k, area[t]));
-}
-
 // One thread: per-mesh point totals from the inclusive scan of the counts.
 __global__ void k_lattice_mesh_counts(const unsigned long long* __restrict__ C, const int64_t* __restrict__ tri_off,
                                       int32_t M, int64_t* __restrict__ counts)
@@ -374,11 +354,6 @@ void launch_sample_guide(const unsigned long long* C, const int64_t* tri_off, co
                          const int32_t* gsh, int32_t M, int64_t G, int32_t* guide, hipStream_t s)
 {
     if (G > 0) k_sample_guide<<<grid_for(G), kBlock, 0, s>>>(C, tri_off, goff, gsh, M, G, guide);
-}
-
-void launch_lattice_count(const double* area, int64_t T, double k, unsigned long long* cnt, hipStream_t s)
-{
-    if (T > 0) k_lattice_count<<<grid_for(T), kBlock, 0, s>>>(area, T, k, cnt);
 }
 
 void launch_lattice_mesh_counts(const unsigned long long* C, const int64_t* tri_off, int32_t M, int64_t* counts,

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include "gm_internal.h"
+#include "gm_lattice.h"
 
 namespace gm {
 namespace {
@@ -61,6 +62,26 @@ __device__ __forceinline__ void load_items(const T* in, int64_t base, int64_t n,
     }
 }
 
+// Where a scan's elements come from: an array, or the lattice sampler's point counts of the
+// triangles, formed from their areas where they are scanned (no pass that writes them first).
+template <typename T>
+struct ArrayItems {
+    const T* in;
+    __device__ __forceinline__ void operator()(int64_t base, int64_t n, T (&v)[kItems]) const { load_items(in, base, n, v); }
+};
+
+struct LatticeItems {
+    const double* area;
+    double k;
+    __device__ __forceinline__ void operator()(int64_t base, int64_t n, unsigned long long (&v)[kItems]) const
+    {
+        alignas(16) double a[kItems];
+        load_items(area, base, n, a);
+#pragma unroll
+        for (int i = 0; i < kItems; ++i) v[i] = base + i < n ? lattice_count(k, a[i]) : 0ull;
+    }
+};
+
 // the running sums of those elements from `run` on
 template <bool Inclusive, typename T>
 __device__ __forceinline__ void store_scan(T* out, int64_t base, int64_t n, T (&v)[kItems], T run)
@@ -82,12 +103,12 @@ __device__ __forceinline__ void store_scan(T* out, int64_t base, int64_t n, T (&
     }
 }
 
-template <typename T>
-__global__ void __launch_bounds__(kThreads) k_block_totals(const T* __restrict__ in, int64_t n, T* __restrict__ totals)
+template <typename T, class Items>
+__global__ void __launch_bounds__(kThreads) k_block_totals(Items in, int64_t n, T* __restrict__ totals)
 {
     const int64_t base = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kItems;
     alignas(16) T v[kItems];
-    load_items(in, base, n, v);
+    in(base, n, v);
     T s = 0;
 #pragma unroll
     for (int i = 0; i < kItems; ++i) s += v[i];
@@ -100,14 +121,14 @@ __global__ void __launch_bounds__(kThreads) k_block_totals(const T* __restrict__
 // (8,192 totals: 20 us by 256 threads, one each; 5 us this way).
 constexpr int kOneThreads = 1024;
 
-template <typename T, bool Inclusive>
-__global__ void __launch_bounds__(kOneThreads) k_scan_one(const T* in, T* out, int64_t n)
+template <typename T, bool Inclusive, class Items>
+__global__ void __launch_bounds__(kOneThreads) k_scan_one(Items in, T* out, int64_t n)
 {
     T carry = 0;
     for (int64_t b0 = 0; b0 < n; b0 += kOneThreads * kItems) {
         const int64_t base = b0 + (int64_t)threadIdx.x * kItems;
         alignas(16) T v[kItems];
-        load_items(in, base, n, v);
+        in(base, n, v);
         T s = 0;
 #pragma unroll
         for (int i = 0; i < kItems; ++i) s += v[i];
@@ -118,13 +139,13 @@ __global__ void __launch_bounds__(kOneThreads) k_scan_one(const T* in, T* out, i
     }
 }
 
-template <typename T, bool Inclusive>
-__global__ void __launch_bounds__(kThreads) k_block_scan(const T* __restrict__ in, T* __restrict__ out, int64_t n,
+template <typename T, bool Inclusive, class Items>
+__global__ void __launch_bounds__(kThreads) k_block_scan(Items in, T* __restrict__ out, int64_t n,
                                                          const T* __restrict__ offsets)
 {
     const int64_t base = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kItems;
     alignas(16) T v[kItems];
-    load_items(in, base, n, v);
+    in(base, n, v);
     T s = 0;
 #pragma unroll
     for (int i = 0; i < kItems; ++i) s += v[i];
@@ -133,21 +154,21 @@ __global__ void __launch_bounds__(kThreads) k_block_scan(const T* __restrict__ i
     store_scan<Inclusive>(out, base, n, v, run);
 }
 
-template <typename T, bool Inclusive>
-void scan(const T* in, T* out, int64_t n, void* tmp, hipStream_t s)
+template <typename T, bool Inclusive, class Items>
+void scan(Items in, T* out, int64_t n, void* tmp, hipStream_t s)
 {
     if (n <= 0) return;
     // one launch where one block takes no longer than three (32,768 elements: 7.4 us; 8 us and
     // two more launches otherwise)
     if (n <= 4 * kOneThreads * kItems) {
-        k_scan_one<T, Inclusive><<<1, kOneThreads, 0, s>>>(in, out, n);
+        k_scan_one<T, Inclusive, Items><<<1, kOneThreads, 0, s>>>(in, out, n);
         return;
     }
     const int64_t nb = (n + kTile - 1) / kTile;
     T* totals = static_cast<T*>(tmp);
-    k_block_totals<T><<<(unsigned)nb, kThreads, 0, s>>>(in, n, totals);
-    k_scan_one<T, false><<<1, kOneThreads, 0, s>>>(totals, totals, nb);
-    k_block_scan<T, Inclusive><<<(unsigned)nb, kThreads, 0, s>>>(in, out, n, totals);
+    k_block_totals<T, Items><<<(unsigned)nb, kThreads, 0, s>>>(in, n, totals);
+    k_scan_one<T, false><<<1, kOneThreads, 0, s>>>(ArrayItems<T>{totals}, totals, nb);
+    k_block_scan<T, Inclusive, Items><<<(unsigned)nb, kThreads, 0, s>>>(in, out, n, totals);
 }
 
 }  // namespace
@@ -161,12 +182,17 @@ size_t scan_tmp_bytes(int64_t n)
 void launch_inclusive_scan_u64(const unsigned long long* in, unsigned long long* out, int64_t n, void* tmp,
                                hipStream_t s)
 {
-    scan<unsigned long long, true>(in, out, n, tmp, s);
+    scan<unsigned long long, true>(ArrayItems<unsigned long long>{in}, out, n, tmp, s);
+}
+
+void launch_lattice_scan(const double* area, double k, unsigned long long* out, int64_t n, void* tmp, hipStream_t s)
+{
+    scan<unsigned long long, true>(LatticeItems{area, k}, out, n, tmp, s);
 }
 
 void launch_exclusive_scan_u32(const uint32_t* in, uint32_t* out, int64_t n, void* tmp, hipStream_t s)
 {
-    scan<uint32_t, false>(in, out, n, tmp, s);
+    scan<uint32_t, false>(ArrayItems<uint32_t>{in}, out, n, tmp, s);
 }
 
 }  // namespace gm
