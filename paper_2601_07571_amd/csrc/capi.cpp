@@ -180,17 +180,13 @@ gm_status lattice_counts(gm_scene* sc, double k, hipStream_t s, std::vector<int6
     return GM_OK;
 }
 
-// the solid-box tree of the meshes whose closed flag is set, with its octant copies
-hipError_t upload_solid(gm_scene* sc)
+// mesh m's entry of DensityLaunch::solid_mbox under its present flag
+void solid_mbox_entry(const gm_scene* sc, int32_t m, float (&e)[8])
 {
-    std::vector<BvhNode> nodes, node8;
-    build_solid_tree(sc->solid_boxes, sc->closed, nodes);
-    sc->solid_n = (int64_t)nodes.size();
-    if (nodes.empty()) return hipSuccess;
-    octant_node_copies(nodes, node8);
-    const hipError_t e = sc->solid.ensure(node8.size() * sizeof(BvhNode));
-    if (e != hipSuccess) return e;
-    return hipMemcpy(sc->solid.p, node8.data(), node8.size() * sizeof(BvhNode), hipMemcpyHostToDevice);
+    for (int c = 0; c < 8; ++c) {
+        const float open = (c & 3) == 3 ? 0.0f : (c < 4 ? -INFINITY : INFINITY);
+        e[c] = sc->closed[(size_t)m] ? sc->mbox[(size_t)8 * m + c] : open;
+    }
 }
 
 bool finite3(const float* p) { return std::isfinite(p[0]) && std::isfinite(p[1]) && std::isfinite(p[2]); }
@@ -334,10 +330,10 @@ void density_args(const gm_scene* sc, const DensityWork& w, int64_t n, int32_t F
             a.hz_reach = sc->hz_reach;
         }
     }
-    if (mode != GM_OCC_NONE && sc->solid_n > 0) {
+    if (mode != GM_OCC_NONE && sc->solid_n > 0 && sc->any_closed()) {
         a.solid = sc->solid.as<BvhNode>();
         a.solid_stride = sc->solid_n;
-        a.mbox = sc->mbox_d.as<float4>();
+        a.solid_mbox = sc->solid_mbox_d.as<float4>();
     }
 }
 
@@ -541,6 +537,8 @@ gm_status gm_scene_create(const gm_mesh* meshes, int32_t n_meshes, gm_scene** ou
         sc->hz_reach = (float)(4.0 * sum / (3.0 * (double)T));
     }
     sc->closed_topology = sc->closed;
+    sc->mbox = mbox;
+    std::vector<BvhNode> solid8;
     {
         double scale = 0.0;
         for (int c = 0; c < 3; ++c)
@@ -548,9 +546,20 @@ gm_status gm_scene_create(const gm_mesh* meshes, int32_t n_meshes, gm_scene** ou
         int32_t n_closed = 0;
         for (uint8_t c : sc->closed) n_closed += c;
         const int most = std::max(kSolidLeast, std::min(kSolidMost, kSolidScene / std::max(1, n_closed)));
+        std::vector<SolidBox> boxes;
         for (int32_t m = 0; m < n_meshes; ++m)
             if (sc->closed[(size_t)m])
-                solid_boxes(meshes[m].vertices, meshes[m].indices, meshes[m].n_triangles, scale, most, m, sc->solid_boxes);
+                solid_boxes(meshes[m].vertices, meshes[m].indices, meshes[m].n_triangles, scale, most, m, boxes);
+        std::vector<BvhNode> nodes;
+        build_solid_tree(std::move(boxes), nodes);
+        sc->solid_n = (int64_t)nodes.size();
+        if (sc->solid_n > 0) octant_node_copies(nodes, solid8);
+    }
+    std::vector<float> solid_mbox((size_t)8 * n_meshes);
+    for (int32_t m = 0; m < n_meshes; ++m) {
+        float v[8];
+        solid_mbox_entry(sc, m, v);
+        std::copy(v, v + 8, solid_mbox.begin() + (size_t)8 * m);
     }
     {
         double d2 = 0.0;
@@ -576,7 +585,8 @@ gm_status gm_scene_create(const gm_mesh* meshes, int32_t n_meshes, gm_scene** ou
     if (e == hipSuccess) e = up(sc->tris, tri3.data(), tri3.size() * sizeof(BvhTri));
     if (e == hipSuccess) e = up(sc->closed_d, sc->closed.data(), sc->closed.size());
     if (e == hipSuccess) e = up(sc->mbox_d, mbox.data(), mbox.size() * 4);
-    if (e == hipSuccess) e = upload_solid(sc);
+    if (e == hipSuccess && sc->solid_n > 0) e = up(sc->solid, solid8.data(), solid8.size() * sizeof(BvhNode));
+    if (e == hipSuccess) e = up(sc->solid_mbox_d, solid_mbox.data(), solid_mbox.size() * 4);
     if (e != hipSuccess) {
         delete sc;
         return fail(e == hipErrorOutOfMemory ? GM_ERR_OUT_OF_MEMORY : GM_ERR_DEVICE, "scene upload: %s",
@@ -633,7 +643,9 @@ gm_status gm_scene_set_mesh_closed(gm_scene* sc, int32_t mesh, int32_t closed)
     GM_HIP(hipDeviceSynchronize());
     sc->closed[(size_t)mesh] = closed ? 1 : 0;
     GM_HIP(hipMemcpy(sc->closed_d.as<uint8_t>() + mesh, &sc->closed[(size_t)mesh], 1, hipMemcpyHostToDevice));
-    GM_HIP(upload_solid(sc));
+    float v[8];
+    solid_mbox_entry(sc, mesh, v);
+    GM_HIP(hipMemcpy(sc->solid_mbox_d.as<float>() + (size_t)8 * mesh, v, sizeof(v), hipMemcpyHostToDevice));
     return GM_OK;
 }
 
@@ -801,6 +813,7 @@ gm_status gm_debug_pair_visibility(gm_scene* sc, const float* pos, const int32_t
         bf.rmax = sc->bf_rmax;
         bf.l2max = backface_l2max(sc);
         if (sc->solid_n > 0) bf.solid = sc->solid.as<BvhNode>();
+        bf.solid_mbox = sc->solid_mbox_d.as<float4>();
     }
     launch_pair_visibility(pos, tri, mesh, sc->tri_mesh.as<int32_t>(), eye, gaze, pair_s, pair_f, m, n_points, n_eyes,
                            sc->T, sc->nodes.as<BvhNode>(), sc->tris.as<BvhTri>() + 2 * sc->bvh.tris.size(),

@@ -177,11 +177,12 @@ struct gm_scene {
     DevBuf closed_d, mbox_d;
     float bf_rmax = 0.0f;
     float hz_reach = 0.0f;  // distance from a point within which its horizon holds every triangle
-    // boxes inside the closed meshes and the tree over those whose flag is set (octant
-    // copies; solid_n nodes a copy, 0: none)
-    std::vector<gm::SolidBox> solid_boxes;
-    DevBuf solid;
+    // the tree over the boxes inside the meshes that gm_mesh_closed passed (octant copies;
+    // solid_n nodes a copy, 0: none) and those meshes' bounding boxes as the boxes' rule reads
+    // them (see DensityLaunch::solid_mbox); mbox: host copy of mbox_d
+    DevBuf solid, solid_mbox_d;
     int64_t solid_n = 0;
+    std::vector<float> mbox;
     bool any_closed() const
     {
         for (uint8_t c : closed)

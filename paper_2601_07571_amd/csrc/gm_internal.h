@@ -84,9 +84,9 @@ struct SolidBox {
 // scene_scale: largest coordinate magnitude of the scene
 void solid_boxes(const float* V, const int32_t* I, int64_t T, double scene_scale, int max_boxes, int32_t mesh,
                  std::vector<SolidBox>& out);
-// a tree over the boxes of the meshes whose flag is set, in BvhNode form: child >= 0 a node,
-// count 1 and child ~m a box of mesh m; empty when there is none
-void build_solid_tree(const std::vector<SolidBox>& boxes, const std::vector<uint8_t>& closed, std::vector<BvhNode>& nodes);
+// a tree over the boxes in BvhNode form: child >= 0 a node, count 1 and child ~m a box of mesh
+// m; empty when there is none
+void build_solid_tree(std::vector<SolidBox> boxes, std::vector<BvhNode>& nodes);
 
 // ---------------------------------------------------------------------------
 // Launchers (defined in the .hip files).  All asynchronous on `s`.
@@ -221,9 +221,13 @@ struct DensityLaunch {
     const float* hz = nullptr;
     float hz_reach = 0.0f;
     // The solid-box rule (static scenes; NULL: off): kNodeCopies octant copies of the tree
-    // over the boxes inside closed meshes, solid_stride nodes apart; uses mbox.
+    // over the boxes inside closed meshes, solid_stride nodes apart, both fixed at scene
+    // creation; solid_mbox: mbox, unbounded for a mesh whose closed flag is cleared (no eye is
+    // outside it, which takes its boxes out).  A flag changes solid_mbox in place, so launches
+    // that were planned or captured before follow it.
     const BvhNode* solid = nullptr;
     int64_t solid_stride = 0;
+    const float4* solid_mbox = nullptr;
 };
 
 // Triangles of its own mesh listed per point for the back-face rule (more: the rule
@@ -288,6 +292,7 @@ struct BackfaceArgs {
     float rmax = 0.0f;
     float l2max = 0.0f;
     const BvhNode* solid = nullptr;  // plain copy of the solid-box tree (NULL: none)
+    const float4* solid_mbox = nullptr;
 };
 void launch_pair_visibility(const float* pos, const int32_t* tri, const int32_t* mesh, const int32_t* tri_mesh,
                             const float* eye, const float* gaze, const int32_t* ps, const int32_t* pf, int64_t m,

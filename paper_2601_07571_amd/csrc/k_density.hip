@@ -489,8 +489,9 @@ __device__ void occluded_packet(const BvhNode* __restrict__ nodes, const BvhTri*
 // The solid-box rule.  A segment that meets a box inside a closed mesh M (no triangle of M
 // in it, M winding around it), where occluders count (t in [kTlo, 1]), on its way to an eye
 // outside M's bounding box crosses M beyond the box: it is occluded, by a triangle other
-// than the point's own (the box keeps its distance from every triangle).  The packet walks
-// the tree over those boxes (a few hundred at most: it stays in the scalar cache) as
+// than the point's own (the box keeps its distance from every triangle).  mbox: those
+// bounding boxes, unbounded for a mesh whose closed flag is cleared.  The packet walks
+// the tree over the solid boxes (a few hundred at most: it stays in the scalar cache) as
 // occluded_packet walks the triangles'; a lane is done at its first box.  An occluded
 // packet then costs a few node visits instead of a descent to the triangles.
 // Returns the lanes of `live` that are occluded.
@@ -915,6 +916,7 @@ struct BfArgs {
     float hz_reach;
     const BvhNode* solid;
     int64_t solid_stride;
+    const float4* solid_mbox;
     float l2max;
 };
 
@@ -1798,7 +1800,7 @@ __device__ __forceinline__ void packet_visibility(const BfArgs* bf, const BvhNod
         const int oct = (nx_m != 0 ? 1 : 0) | (ny_m != 0 ? 2 : 0) | (nz_m != 0 ? 4 : 0);
         if (sn) {
             const BvhNode* so = sn + (oct ^ 7) * (int64_t)__builtin_amdgcn_readfirstlane((int)bf->solid_stride);
-            const float4* mb = uniform_ptr(bf->mbox);
+            const float4* mb = uniform_ptr(bf->solid_mbox);
 #pragma unroll
             for (int k = 0; k < SPL; ++k) {
                 solid[k] = __builtin_amdgcn_inverse_ballot_w64(
@@ -1821,7 +1823,7 @@ __device__ __forceinline__ void packet_visibility(const BfArgs* bf, const BvhNod
         const int lead = __builtin_ctzll(nx_m | px_m);
         const int oct = (int)((nx_m >> lead) & 1) | (int)(((ny_m >> lead) & 1) << 1) | (int)(((nz_m >> lead) & 1) << 2);
         if (sn) {
-            const float4* mb = uniform_ptr(bf->mbox);
+            const float4* mb = uniform_ptr(bf->solid_mbox);
 #pragma unroll
             for (int k = 0; k < SPL; ++k) {
                 solid[k] = __builtin_amdgcn_inverse_ballot_w64(
@@ -1910,7 +1912,7 @@ __device__ __forceinline__ void density_item(const DensityLaunch& a, int64_t til
         s_o4 = o4;
     }
     if (threadIdx.x < kDensityStats) s_stats[threadIdx.x] = 0u;
-    if (OCC != 0 && !ZB && threadIdx.x == 0) s_bf = BfArgs{a.bface, a.bcand, a.mbox, a.bf_tris, a.hz, a.hz_reach, a.solid, a.solid_stride, a.bf_L2max};
+    if (OCC != 0 && !ZB && threadIdx.x == 0) s_bf = BfArgs{a.bface, a.bcand, a.mbox, a.bf_tris, a.hz, a.hz_reach, a.solid, a.solid_stride, a.solid_mbox, a.bf_L2max};
     __syncthreads();
     uint32_t n_in = 0, n_vis = 0, n_trav = 0, n_bf = 0;  // wave-uniform counters
     TravCount n_visits;
@@ -2384,7 +2386,7 @@ __global__ void __launch_bounds__(64) k_pair_visibility(const float* __restrict_
         }
     }
     if (bf.solid && mode != 0 &&
-        solid_packet<false>(bf.solid, bf.mbox, oct, sgs[0], ex, ey, ez, me, mode, 1ull, visits) != 0) {
+        solid_packet<false>(bf.solid, bf.solid_mbox, oct, sgs[0], ex, ey, ez, me, mode, 1ull, visits) != 0) {
         if (lane == 0) vis[i] = 0;
         return;
     }

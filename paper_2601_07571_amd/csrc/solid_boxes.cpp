@@ -270,13 +270,10 @@ int32_t build_solid(std::vector<SolidBox>& b, int64_t first, int64_t last, std::
 
 }  // namespace
 
-void build_solid_tree(const std::vector<SolidBox>& boxes, const std::vector<uint8_t>& closed, std::vector<BvhNode>& nodes)
+void build_solid_tree(std::vector<SolidBox> boxes, std::vector<BvhNode>& nodes)
 {
     nodes.clear();
-    std::vector<SolidBox> b;
-    for (const SolidBox& s : boxes)
-        if (closed[(size_t)s.mesh]) b.push_back(s);
-    if (!b.empty()) (void)build_solid(b, 0, (int64_t)b.size(), nodes);
+    if (!boxes.empty()) (void)build_solid(boxes, 0, (int64_t)boxes.size(), nodes);
 }
 
 }  // namespace gm
