@@ -329,11 +329,11 @@ void density_args(const gm_scene* sc, const DensityWork& w, int64_t n, int32_t F
             a.hz = w.hz.as<float>();
             a.hz_reach = sc->hz_reach;
         }
-    }
-    if (mode != GM_OCC_NONE && sc->solid_n > 0 && sc->any_closed()) {
-        a.solid = sc->solid.as<BvhNode>();
-        a.solid_stride = sc->solid_n;
-        a.solid_mbox = sc->solid_mbox_d.as<float4>();
+        if (sc->solid_n > 0 && sc->any_closed()) {
+            a.solid = sc->solid.as<BvhNode>();
+            a.solid_stride = sc->solid_n;
+            a.solid_mbox = sc->solid_mbox_d.as<float4>();
+        }
     }
 }
 
@@ -353,7 +353,8 @@ gm_status density_backface(gm_scene* sc, DensityWork& w, int64_t n, uint32_t mod
     GM_HIP(w.bcand.ensure(4 * (size_t)kBfCand * (size_t)(off + n)));
     launch_backface_prep(w.spos.as<float4>() + off, w.smesh.as<int32_t>() + off, n, sc->V.as<float>(),
                          sc->I.as<int32_t>(), sc->closed_d.as<uint8_t>(), sc->nodes.as<BvhNode>(),
-                         sc->tris.as<BvhTri>() + 2 * sc->bvh.tris.size(), sc->bf_rmax, w.bface.as<float4>() + off,
+                         sc->tris.as<BvhTri>() + 2 * sc->bvh.tris.size(), sc->bf_rmax, sc->solid_near,
+                         w.bface.as<float4>() + off,
                          w.bcand.as<int32_t>() + kBfCand * off, s);
     GM_HIP(hipGetLastError());
     w.backface = true;
@@ -546,10 +547,13 @@ gm_status gm_scene_create(const gm_mesh* meshes, int32_t n_meshes, gm_scene** ou
         int32_t n_closed = 0;
         for (uint8_t c : sc->closed) n_closed += c;
         const int most = std::max(kSolidLeast, std::min(kSolidMost, kSolidScene / std::max(1, n_closed)));
+        double near = INFINITY;
         std::vector<SolidBox> boxes;
         for (int32_t m = 0; m < n_meshes; ++m)
             if (sc->closed[(size_t)m])
-                solid_boxes(meshes[m].vertices, meshes[m].indices, meshes[m].n_triangles, scale, most, m, boxes);
+                near = std::min(near, solid_boxes(meshes[m].vertices, meshes[m].indices, meshes[m].n_triangles, scale,
+                                                  most, m, boxes));
+        sc->solid_near = (float)(0.5 * near);
         std::vector<BvhNode> nodes;
         build_solid_tree(std::move(boxes), nodes);
         sc->solid_n = (int64_t)nodes.size();
@@ -812,6 +816,7 @@ gm_status gm_debug_pair_visibility(gm_scene* sc, const float* pos, const int32_t
         bf.mbox = sc->mbox_d.as<float4>();
         bf.rmax = sc->bf_rmax;
         bf.l2max = backface_l2max(sc);
+        bf.near = sc->solid_near;
         if (sc->solid_n > 0) bf.solid = sc->solid.as<BvhNode>();
         bf.solid_mbox = sc->solid_mbox_d.as<float4>();
     }

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstdarg>
 #include <cstdint>
 #include <string>
@@ -182,6 +183,7 @@ struct gm_scene {
     // them (see DensityLaunch::solid_mbox); mbox: host copy of mbox_d
     DevBuf solid, solid_mbox_d;
     int64_t solid_n = 0;
+    float solid_near = INFINITY;  // half the least distance of a box from its mesh's triangles
     std::vector<float> mbox;
     bool any_closed() const
     {

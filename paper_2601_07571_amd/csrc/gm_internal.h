@@ -81,8 +81,9 @@ struct SolidBox {
     int32_t mesh;
 };
 // at most max_boxes boxes of one closed mesh (vertices V, its own triangles I [T][3]);
-// scene_scale: largest coordinate magnitude of the scene
-void solid_boxes(const float* V, const int32_t* I, int64_t T, double scene_scale, int max_boxes, int32_t mesh,
+// scene_scale: largest coordinate magnitude of the scene.  Returns the distance that every
+// box of the mesh keeps from its triangles.
+double solid_boxes(const float* V, const int32_t* I, int64_t T, double scene_scale, int max_boxes, int32_t mesh,
                  std::vector<SolidBox>& out);
 // a tree over the boxes in BvhNode form: child >= 0 a node, count 1 and child ~m a box of mesh
 // m; empty when there is none
@@ -205,9 +206,10 @@ struct DensityLaunch {
     // The back-face rule (static scenes; NULL bface: off).  Per sorted point: the unit
     // normal of its own triangle times the point's distance to that triangle's edges
     // and, in w, the number of triangles of its mesh within
-    // bf_rmax of it (as int bits, low byte; -1: the rule does not apply to the point), whose
-    // record indices (plain x, y, z copy) are bcand[kBfCand * i + j], and above it 16 bits
-    // of the steepest slope below the plane that they reach (as sin^2; all ones: any).  mbox: per mesh the
+    // bf_rmax of it (as int bits, low byte; the sign: the rule does not apply to the point), whose
+    // record indices (plain x, y, z copy) are bcand[kBfCand * i + j], above it 16 bits
+    // of the steepest slope below the plane that they reach (as sin^2; all ones: any), and above
+    // those a bit: the point lies within `near` of its triangle, or has none.  mbox: per mesh the
     // bounding box, lo then hi (2 float4).  A segment longer than sqrt(bf_L2max) is left
     // to the traversal.
     const float4* bface = nullptr;
@@ -291,6 +293,7 @@ struct BackfaceArgs {
     const float4* mbox = nullptr;
     float rmax = 0.0f;
     float l2max = 0.0f;
+    float near = 0.0f;
     const BvhNode* solid = nullptr;  // plain copy of the solid-box tree (NULL: none)
     const float4* solid_mbox = nullptr;
 };
@@ -411,9 +414,10 @@ bool mesh_is_closed(const float* V, int64_t nv, const int32_t* I, int64_t T);
 // Per sorted point, the data of the back-face rule (see DensityLaunch::bface): normal of
 // its own triangle and the triangles of its mesh whose boxes come within rmax of it,
 // found by a packet walk of the scene BVH (plain node copy `nodes`, record copy `tris`
-// in x, y, z order).  closed [M] (device): meshes the rule may use.
+// in x, y, z order).  closed [M] (device): meshes the rule may use.  near: see
+// DensityLaunch::bface.
 void launch_backface_prep(const float4* spos, const int32_t* smesh, int64_t n, const float* V, const int32_t* I,
-                          const uint8_t* closed, const BvhNode* nodes, const BvhTri* tris, float rmax,
+                          const uint8_t* closed, const BvhNode* nodes, const BvhTri* tris, float rmax, float near,
                           float4* bface, int32_t* bcand, hipStream_t s);
 // Per sorted point the horizon of the triangles within `reach` of it above its own
 // triangle's plane (see DensityLaunch::hz), from the normals in bface.

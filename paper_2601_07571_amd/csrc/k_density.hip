@@ -155,7 +155,7 @@ struct Seg {
     float qx, qy, qz;  // -x / direction
     float sx, sy;      // watertight shear: d[kx] / d[kz], d[ky] / d[kz]
     float tz;          // d[kz]
-    float t0;          // the walk's box tests begin here (at least kTlo)
+    float t0;          // the walk's box tests begin here (kTlo, beyond it, or 0)
     int kx, ky, kz;    // axis order of the shear
 };
 
@@ -211,7 +211,7 @@ __device__ __forceinline__ int segment_axis(int gz, float dx, float dy, float dz
 }
 
 // Segment from the point x (t = 0) to the eye e (t = 1), sheared along the given axis
-// order; the slab tests of box_hit_signed01 / box_hit01 clamp to [kTlo, 1].
+// order; the slab tests of box_hit_signed01 / box_hit01 clamp to [t0, 1].
 __device__ __forceinline__ Seg make_seg(float xx, float xy, float xz, float ex, float ey, float ez, int kx, int ky,
                                         int kz)
 {
@@ -488,8 +488,11 @@ __device__ void occluded_packet(const BvhNode* __restrict__ nodes, const BvhTri*
 // ---------------------------------------------------------------------------
 // The solid-box rule.  A segment that meets a box inside a closed mesh M (no triangle of M
 // in it, M winding around it), where occluders count (t in [kTlo, 1]), on its way to an eye
-// outside M's bounding box crosses M beyond the box: it is occluded, by a triangle other
-// than the point's own (the box keeps its distance from every triangle).  mbox: those
+// outside M's bounding box crosses M beyond the box: it is occluded.  A triangle does not
+// occlude its own points, but the crossing is not the point's own triangle when the point lies
+// closer to that than the box does: on a segment that ends on the triangle, the distance to it
+// (a convex set) is nowhere larger than at its start.  So the rule is for points within
+// solid_near of their triangle (half the least distance of a box), or without one.  mbox: those
 // bounding boxes, unbounded for a mesh whose closed flag is cleared.  The packet walks
 // the tree over the solid boxes (a few hundred at most: it stays in the scalar cache) as
 // occluded_packet walks the triangles'; a lane is done at its first box.  An occluded
@@ -678,16 +681,19 @@ __device__ __forceinline__ float box_dist2(float x, float y, float z, const floa
 // it, by one packet walk of the scene BVH per wave (wave-uniform node, the lane's sphere
 // against both child boxes; squared distances against rmax^2 widened by 1e-3).  cnt =
 // -1: the rule does not apply (no closed mesh, degenerate triangle, more than kBfCand
-// neighbours).  The normal is given for points of open meshes too (the horizon rule).  Every lane of the wave must call it.
+// neighbours).  The normal is given for points of open meshes too (the horizon rule).  own: the
+// point has no triangle of its own or lies within `near` of it (the solid-box rule).  Every
+// lane of the wave must call it.
 __device__ __forceinline__ void backface_point(float px, float py, float pz, int t, int m, bool on,
                                                const float* __restrict__ V, const int32_t* __restrict__ I,
                                                const uint8_t* __restrict__ closed,
                                                const BvhNode* __restrict__ nodes, const BvhTri* __restrict__ tris,
-                                               float rmax, float& nx, float& ny, float& nz, float& below, int& cnt,
-                                               int (&cand)[kBfCand])
+                                               float rmax, float near, float& nx, float& ny, float& nz,
+                                               float& below, bool& own, int& cnt, int (&cand)[kBfCand])
 {
     const int lane = lane_id();
     nx = ny = nz = 0.0f;
+    own = on && t < 0;
     on = on && t >= 0;
     if (on) {
         const int i0 = I[3 * t], i1 = I[3 * t + 1], i2 = I[3 * t + 2];
@@ -717,6 +723,12 @@ __device__ __forceinline__ void backface_point(float px, float py, float pz, int
         // D = min over edges of b_i |n| / e_i = a_i / (|n| e_i)
         const float D = fminf(fminf(fmaxf(a0, 0.0f) / e0, fmaxf(a1, 0.0f) / e1), fmaxf(a2, 0.0f) / e2) * inv;
         on = on && D > 0.0f && isfinite(D);
+        // distance to the triangle, from above: to the point of it that the barycentrics without
+        // their negative parts give
+        const float b0 = fmaxf(a0, 0.0f), b1 = fmaxf(a1, 0.0f), b2 = fmaxf(a2, 0.0f), bi = 1.0f / (b0 + b1 + b2);
+        const float qx = wx - (b1 * ux + b2 * vx) * bi, qy = wy - (b1 * uy + b2 * vy) * bi,
+                    qz = wz - (b1 * uz + b2 * vz) * bi;
+        own = __builtin_fmaf(qx, qx, __builtin_fmaf(qy, qy, qz * qz)) <= near * near;
         const float sc = on ? inv * D : 0.0f;
         nx *= sc; ny *= sc; nz *= sc;
     }
@@ -781,11 +793,13 @@ __device__ __forceinline__ void backface_point(float px, float py, float pz, int
     below = hz_sin2(P.H);
 }
 
-// cnt (-1, or 0 .. kBfCand) and the neighbours' sin^2 below the plane (16 bits, rounded up;
-// all ones: none), as kept in bface.w
-__device__ __forceinline__ int pack_neighbours(int cnt, float below)
+// cnt (-1, or 0 .. kBfCand), the neighbours' sin^2 below the plane (16 bits, rounded up;
+// all ones: none) and `own`, as kept in bface.w: negative where the back-face rule is off
+constexpr int kOwnBit = 1 << 24;
+
+__device__ __forceinline__ int pack_neighbours(int cnt, float below, bool own)
 {
-    return cnt < 0 ? -1 : (cnt | ((int)fminf(ceilf(below * 65534.0f), 65535.0f) << 8));
+    return (cnt < 0 ? INT32_MIN : (cnt | ((int)fminf(ceilf(below * 65534.0f), 65535.0f) << 8))) | (own ? kOwnBit : 0);
 }
 
 __device__ __forceinline__ float unpack_below(int w)
@@ -813,8 +827,9 @@ __global__ void __launch_bounds__(256) k_backface_prep(const float4* __restrict_
                                                        const float* __restrict__ V, const int32_t* __restrict__ I,
                                                        const uint8_t* __restrict__ closed,
                                                        const BvhNode* __restrict__ nodes,
-                                                       const BvhTri* __restrict__ tris, float rmax, int lg,
-                                                       float4* __restrict__ bface, int32_t* __restrict__ bcand)
+                                                       const BvhTri* __restrict__ tris, float rmax, float near,
+                                                       int lg, float4* __restrict__ bface,
+                                                       int32_t* __restrict__ bcand)
 {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int lane = (int)(g & 63);
@@ -826,11 +841,12 @@ __global__ void __launch_bounds__(256) k_backface_prep(const float4* __restrict_
         m = smesh[i];
     }
     float nx, ny, nz, below;
+    bool own;
     int cnt, cand[kBfCand];
-    backface_point(p.x, p.y, p.z, __float_as_int(p.w), m, i < n, V, I, closed, nodes, tris, rmax, nx, ny, nz, below, cnt,
-                   cand);
+    backface_point(p.x, p.y, p.z, __float_as_int(p.w), m, i < n, V, I, closed, nodes, tris, rmax, near, nx, ny, nz, below,
+                   own, cnt, cand);
     if (i < n) {
-        bface[i] = make_float4(nx, ny, nz, __int_as_float(pack_neighbours(cnt, below)));
+        bface[i] = make_float4(nx, ny, nz, __int_as_float(pack_neighbours(cnt, below, own)));
 #pragma unroll
         for (int j = 0; j < kBfCand; ++j)
             if (j < cnt) bcand[kBfCand * i + j] = cand[j];
@@ -1118,14 +1134,16 @@ __global__ void __launch_bounds__(256) k_horizon_wide(const float4* __restrict__
 
 // What the rules say of point i (sorted order) and eye e: true when the pair is occluded by
 // the point's own closed mesh; else t0 is where the walk of its segment may begin (beyond the
-// part that the horizon clears, else kTlo; 1: all of it is clear).
+// part that the horizon clears, else kTlo; 1: all of it is clear; 0, and no solid boxes, for a
+// point away from its own triangle).
 __device__ __forceinline__ bool settled_by_rule(const BfArgs& s_bf, const int32_t* smesh, uint32_t i, float xx, float xy,
                                                 float xz, float ex, float ey, float ez, float& t0)
 {
-    t0 = kTlo;
     const float4 bf = uniform_ptr(s_bf.bface)[i];
+    const int c = __float_as_int(bf.w);
+    t0 = (c & kOwnBit) ? kTlo : 0.0f;
     const float* hz = uniform_ptr(s_bf.hz);
-    if (hz) {
+    if (hz && t0 > 0.0f) {
         const float ux = ex - xx, uy = ey - xy, uz = ez - xz;
         const float l2 = __builtin_fmaf(ux, ux, __builtin_fmaf(uy, uy, uz * uz));
         if (steeper(hz[i], bf.x, bf.y, bf.z, ux, uy, uz, l2)) {
@@ -1134,7 +1152,6 @@ __device__ __forceinline__ bool settled_by_rule(const BfArgs& s_bf, const int32_
             return false;
         }
     }
-    const int c = __float_as_int(bf.w);
     if (c < 0) return false;
     const int m = smesh[i];
     const int32_t* cand = uniform_ptr(s_bf.bcand) + kBfCand * (int64_t)i;
@@ -1804,7 +1821,7 @@ __device__ __forceinline__ void packet_visibility(const BfArgs* bf, const BvhNod
 #pragma unroll
             for (int k = 0; k < SPL; ++k) {
                 solid[k] = __builtin_amdgcn_inverse_ballot_w64(
-                    solid_packet<true>(so, mb, oct, sg[k], ex, ey, ez, omesh[k], mode, ballot(need[k]), n_visits));
+                    solid_packet<true>(so, mb, oct, sg[k], ex, ey, ez, omesh[k], mode, ballot(need[k] && t0[k] > 0.0f), n_visits));
                 need[k] = need[k] && !solid[k];
             }
         }
@@ -1827,7 +1844,7 @@ __device__ __forceinline__ void packet_visibility(const BfArgs* bf, const BvhNod
 #pragma unroll
             for (int k = 0; k < SPL; ++k) {
                 solid[k] = __builtin_amdgcn_inverse_ballot_w64(
-                    solid_packet<false>(sn, mb, oct, sg[k], ex, ey, ez, omesh[k], mode, ballot(need[k]), n_visits));
+                    solid_packet<false>(sn, mb, oct, sg[k], ex, ey, ez, omesh[k], mode, ballot(need[k] && t0[k] > 0.0f), n_visits));
                 need[k] = need[k] && !solid[k];
             }
         }
@@ -2371,12 +2388,13 @@ __global__ void __launch_bounds__(64) k_pair_visibility(const float* __restrict_
     const bool act[1] = {mode != 0 && lane == 0};
     bool occ[1] = {false};
     const int oct = (signbit(dx) ? 1 : 0) | (signbit(dy) ? 2 : 0) | (signbit(dz) ? 4 : 0);
+    bool own = false;
     if (bf.closed && mode != 0) {
         float nx, ny, nz, below;
         int cnt, cand[kBfCand];
-        backface_point(px, py, pz, t, me, lane == 0, bf.V, bf.I, bf.closed, nodes, tris, bf.rmax, nx, ny, nz, below, cnt,
-                       cand);
-        const int packed = pack_neighbours(cnt, below);
+        backface_point(px, py, pz, t, me, lane == 0, bf.V, bf.I, bf.closed, nodes, tris, bf.rmax, bf.near, nx, ny, nz, below,
+                       own, cnt, cand);
+        const int packed = pack_neighbours(cnt, below, own);
         const bool back = lane == 0 && me >= 0 &&
                           backface_rule(nx, ny, nz, cnt, unpack_below(packed), [&cand](int j) { return cand[j]; }, px, py, pz, ex, ey, ez,
                                         bf.mbox[2 * me], bf.mbox[2 * me + 1], bf.l2max, tris);
@@ -2385,7 +2403,7 @@ __global__ void __launch_bounds__(64) k_pair_visibility(const float* __restrict_
             return;
         }
     }
-    if (bf.solid && mode != 0 &&
+    if (bf.solid && mode != 0 && ballot(own) != 0 &&
         solid_packet<false>(bf.solid, bf.solid_mbox, oct, sgs[0], ex, ey, ez, me, mode, 1ull, visits) != 0) {
         if (lane == 0) vis[i] = 0;
         return;
@@ -2562,13 +2580,13 @@ void launch_pair_values(const float* pos, const FixRec* fix, const int32_t* ps, 
 }
 
 void launch_backface_prep(const float4* spos, const int32_t* smesh, int64_t n, const float* V, const int32_t* I,
-                          const uint8_t* closed, const BvhNode* nodes, const BvhTri* tris, float rmax,
+                          const uint8_t* closed, const BvhNode* nodes, const BvhTri* tris, float rmax, float near,
                           float4* bface, int32_t* bcand, hipStream_t s)
 {
     if (n > 0) {
         const int lg = prep_lanes_log2(n);
         const int64_t waves = (n + (int64_t(1) << lg) - 1) >> lg;
-        k_backface_prep<<<blocks(waves * 64, 256), 256, 0, s>>>(spos, smesh, n, V, I, closed, nodes, tris, rmax, lg,
+        k_backface_prep<<<blocks(waves * 64, 256), 256, 0, s>>>(spos, smesh, n, V, I, closed, nodes, tris, rmax, near, lg,
                                                                 bface, bcand);
     }
 }

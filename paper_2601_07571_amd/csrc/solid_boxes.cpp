@@ -64,10 +64,11 @@ double winding(const float* V, const int32_t* I, int64_t T, const double* p)
 
 }  // namespace
 
-void solid_boxes(const float* V, const int32_t* I, int64_t T, double scene_scale, int max_boxes, int32_t mesh,
-                 std::vector<SolidBox>& out)
+double solid_boxes(const float* V, const int32_t* I, int64_t T, double scene_scale, int max_boxes, int32_t mesh,
+                   std::vector<SolidBox>& out)
 {
-    if (T < 4 || max_boxes < 1) return;
+    const double none = std::numeric_limits<double>::infinity();
+    if (T < 4 || max_boxes < 1) return none;
     double lo[3], hi[3], ext = 0.0;
     for (int a = 0; a < 3; ++a) {
         lo[a] = std::numeric_limits<double>::infinity();
@@ -80,14 +81,14 @@ void solid_boxes(const float* V, const int32_t* I, int64_t T, double scene_scale
             hi[a] = std::max(hi[a], v);
         }
     for (int a = 0; a < 3; ++a) ext = std::max(ext, hi[a] - lo[a]);
-    if (!(ext > 0.0)) return;
+    if (!(ext > 0.0)) return none;
     // the boxes keep this distance from every triangle: far above the rounding of the
     // device's FP32 slab test (a few 1e-7 of the coordinates)
     const double pad = 1e-4 * ext + 1e-5 * scene_scale;
     Grid g;
     const int res = (int)std::min(64.0, std::max(12.0, std::cbrt((double)T)));
     g.cell = ext / res;
-    if (pad > 0.25 * g.cell) return;
+    if (pad > 0.25 * g.cell) return none;
     for (int a = 0; a < 3; ++a) {
         g.n[a] = std::min(res, std::max(1, (int)std::ceil((hi[a] - lo[a]) / g.cell))) + 2;  // one empty cell around
         const double mid = 0.5 * (lo[a] + hi[a]);
@@ -152,7 +153,7 @@ void solid_boxes(const float* V, const int32_t* I, int64_t T, double scene_scale
             any = true;
         }
     }
-    if (!any) return;
+    if (!any) return none;
     // counts of inside cells below a corner (for "is this block all inside"), and the largest
     // inside cube whose upper corner is the cell
     const int mx = g.n[0] + 1, my = g.n[1] + 1;
@@ -214,6 +215,7 @@ void solid_boxes(const float* V, const int32_t* I, int64_t T, double scene_scale
             out.push_back(o);
             ++made;
         }
+    return pad;
 }
 
 namespace {
