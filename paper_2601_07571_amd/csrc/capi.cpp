@@ -352,7 +352,7 @@ gm_status density_backface(gm_scene* sc, DensityWork& w, int64_t n, uint32_t mod
     GM_HIP(w.bface.ensure(16 * (size_t)(off + n)));
     GM_HIP(w.bcand.ensure(4 * (size_t)kBfCand * (size_t)(off + n)));
     launch_backface_prep(w.spos.as<float4>() + off, w.smesh.as<int32_t>() + off, n, sc->V.as<float>(),
-                         sc->I.as<int32_t>(), sc->closed_d.as<uint8_t>(), sc->nodes.as<BvhNode>(),
+                         sc->I.as<int32_t>(), sc->closed_d.as<uint8_t>(), sc->M, sc->nodes.as<BvhNode>(),
                          sc->tris.as<BvhTri>() + 2 * sc->bvh.tris.size(), sc->bf_rmax, sc->solid_near,
                          w.bface.as<float4>() + off,
                          w.bcand.as<int32_t>() + kBfCand * off, s);
@@ -813,6 +813,7 @@ gm_status gm_debug_pair_visibility(gm_scene* sc, const float* pos, const int32_t
         bf.V = sc->V.as<float>();
         bf.I = sc->I.as<int32_t>();
         bf.closed = sc->closed_d.as<uint8_t>();
+        bf.n_meshes = sc->M;
         bf.mbox = sc->mbox_d.as<float4>();
         bf.rmax = sc->bf_rmax;
         bf.l2max = backface_l2max(sc);

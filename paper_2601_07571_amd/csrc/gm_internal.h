@@ -290,6 +290,7 @@ struct BackfaceArgs {
     const float* V = nullptr;
     const int32_t* I = nullptr;
     const uint8_t* closed = nullptr;
+    int32_t n_meshes = 0;
     const float4* mbox = nullptr;
     float rmax = 0.0f;
     float l2max = 0.0f;
@@ -414,11 +415,11 @@ bool mesh_is_closed(const float* V, int64_t nv, const int32_t* I, int64_t T);
 // Per sorted point, the data of the back-face rule (see DensityLaunch::bface): normal of
 // its own triangle and the triangles of its mesh whose boxes come within rmax of it,
 // found by a packet walk of the scene BVH (plain node copy `nodes`, record copy `tris`
-// in x, y, z order).  closed [M] (device): meshes the rule may use.  near: see
+// in x, y, z order).  closed [n_meshes] (device): meshes the rule may use.  near: see
 // DensityLaunch::bface.
 void launch_backface_prep(const float4* spos, const int32_t* smesh, int64_t n, const float* V, const int32_t* I,
-                          const uint8_t* closed, const BvhNode* nodes, const BvhTri* tris, float rmax, float near,
-                          float4* bface, int32_t* bcand, hipStream_t s);
+                          const uint8_t* closed, int32_t n_meshes, const BvhNode* nodes, const BvhTri* tris,
+                          float rmax, float near, float4* bface, int32_t* bcand, hipStream_t s);
 // Per sorted point the horizon of the triangles within `reach` of it above its own
 // triangle's plane (see DensityLaunch::hz), from the normals in bface.
 void launch_horizon(const float4* spos, const float4* bface, int64_t n, const BvhNode* nodes, const BvhTri* tris,

@@ -686,7 +686,7 @@ __device__ __forceinline__ float box_dist2(float x, float y, float z, const floa
 // lane of the wave must call it.
 __device__ __forceinline__ void backface_point(float px, float py, float pz, int t, int m, bool on,
                                                const float* __restrict__ V, const int32_t* __restrict__ I,
-                                               const uint8_t* __restrict__ closed,
+                                               const uint8_t* __restrict__ closed, int32_t n_meshes,
                                                const BvhNode* __restrict__ nodes, const BvhTri* __restrict__ tris,
                                                float rmax, float near, float& nx, float& ny, float& nz,
                                                float& below, bool& own, int& cnt, int (&cand)[kBfCand])
@@ -732,7 +732,8 @@ __device__ __forceinline__ void backface_point(float px, float py, float pz, int
         const float sc = on ? inv * D : 0.0f;
         nx *= sc; ny *= sc; nz *= sc;
     }
-    on = on && m >= 0 && closed[m] != 0;  // the neighbours: closed meshes only
+    // the neighbours: closed meshes only (a mesh id is the caller's and may be any number)
+    on = on && m >= 0 && m < n_meshes && closed[m] != 0;
     const float r2 = rmax * rmax * 1.001f;
     cnt = 0;
 #pragma unroll
@@ -825,7 +826,7 @@ __host__ __device__ constexpr int prep_lanes_log2(int64_t n)
 __global__ void __launch_bounds__(256) k_backface_prep(const float4* __restrict__ spos,
                                                        const int32_t* __restrict__ smesh, int64_t n,
                                                        const float* __restrict__ V, const int32_t* __restrict__ I,
-                                                       const uint8_t* __restrict__ closed,
+                                                       const uint8_t* __restrict__ closed, int32_t n_meshes,
                                                        const BvhNode* __restrict__ nodes,
                                                        const BvhTri* __restrict__ tris, float rmax, float near,
                                                        int lg, float4* __restrict__ bface,
@@ -843,8 +844,8 @@ __global__ void __launch_bounds__(256) k_backface_prep(const float4* __restrict_
     float nx, ny, nz, below;
     bool own;
     int cnt, cand[kBfCand];
-    backface_point(p.x, p.y, p.z, __float_as_int(p.w), m, i < n, V, I, closed, nodes, tris, rmax, near, nx, ny, nz, below,
-                   own, cnt, cand);
+    backface_point(p.x, p.y, p.z, __float_as_int(p.w), m, i < n, V, I, closed, n_meshes, nodes, tris, rmax, near, nx,
+                   ny, nz, below, own, cnt, cand);
     if (i < n) {
         bface[i] = make_float4(nx, ny, nz, __int_as_float(pack_neighbours(cnt, below, own)));
 #pragma unroll
@@ -2392,10 +2393,10 @@ __global__ void __launch_bounds__(64) k_pair_visibility(const float* __restrict_
     if (bf.closed && mode != 0) {
         float nx, ny, nz, below;
         int cnt, cand[kBfCand];
-        backface_point(px, py, pz, t, me, lane == 0, bf.V, bf.I, bf.closed, nodes, tris, bf.rmax, bf.near, nx, ny, nz, below,
-                       own, cnt, cand);
+        backface_point(px, py, pz, t, me, lane == 0, bf.V, bf.I, bf.closed, bf.n_meshes, nodes, tris, bf.rmax, bf.near, nx,
+                       ny, nz, below, own, cnt, cand);
         const int packed = pack_neighbours(cnt, below, own);
-        const bool back = lane == 0 && me >= 0 &&
+        const bool back = lane == 0 && packed >= 0 &&
                           backface_rule(nx, ny, nz, cnt, unpack_below(packed), [&cand](int j) { return cand[j]; }, px, py, pz, ex, ey, ez,
                                         bf.mbox[2 * me], bf.mbox[2 * me + 1], bf.l2max, tris);
         if (ballot(back) != 0) {
@@ -2580,14 +2581,14 @@ void launch_pair_values(const float* pos, const FixRec* fix, const int32_t* ps, 
 }
 
 void launch_backface_prep(const float4* spos, const int32_t* smesh, int64_t n, const float* V, const int32_t* I,
-                          const uint8_t* closed, const BvhNode* nodes, const BvhTri* tris, float rmax, float near,
-                          float4* bface, int32_t* bcand, hipStream_t s)
+                          const uint8_t* closed, int32_t n_meshes, const BvhNode* nodes, const BvhTri* tris,
+                          float rmax, float near, float4* bface, int32_t* bcand, hipStream_t s)
 {
     if (n > 0) {
         const int lg = prep_lanes_log2(n);
         const int64_t waves = (n + (int64_t(1) << lg) - 1) >> lg;
-        k_backface_prep<<<blocks(waves * 64, 256), 256, 0, s>>>(spos, smesh, n, V, I, closed, nodes, tris, rmax, near, lg,
-                                                                bface, bcand);
+        k_backface_prep<<<blocks(waves * 64, 256), 256, 0, s>>>(spos, smesh, n, V, I, closed, n_meshes, nodes, tris,
+                                                                rmax, near, lg, bface, bcand);
     }
 }
 
