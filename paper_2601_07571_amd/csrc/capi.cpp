@@ -361,13 +361,20 @@ gm_status density_backface(gm_scene* sc, DensityWork& w, int64_t n, uint32_t mod
     return GM_OK;
 }
 
+bool stream_captures(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusActive;
+    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 bool horizon_room(DensityWork& w, int64_t n, hipStream_t s)
 {
     const size_t bf = 16 * (size_t)n, bc = 4 * (size_t)kBfCand * (size_t)n, hz = 4 * (size_t)n;
     if (w.bface.bytes >= bf && w.bcand.bytes >= bc && w.hz.bytes >= hz) return true;
-    hipStreamCaptureStatus st = hipStreamCaptureStatusActive;
-    if (hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusNone &&
-        w.bface.ensure(bf) == hipSuccess && w.bcand.ensure(bc) == hipSuccess && w.hz.ensure(hz) == hipSuccess)
+    if (!stream_captures(s) && w.bface.ensure(bf) == hipSuccess && w.bcand.ensure(bc) == hipSuccess &&
+        w.hz.ensure(hz) == hipSuccess)
         return true;
     (void)hipGetLastError();
     return false;

@@ -242,6 +242,8 @@ gm_status density_backface(gm_scene* sc, DensityWork& w, int64_t n, uint32_t mod
                            int64_t off = 0);
 // whether the horizons of n points pay for themselves over F fixations
 bool horizon_pays(int64_t n, int64_t F, double sigma, uint32_t mode);
+// whether s is being captured (or cannot say)
+bool stream_captures(hipStream_t s);
 // whether w holds (or can be given) the buffers of n points' horizons: without them, as in a
 // capture that would have to allocate, the rule is left out
 bool horizon_room(DensityWork& w, int64_t n, hipStream_t s);

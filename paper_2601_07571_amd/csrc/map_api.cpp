@@ -54,8 +54,10 @@ struct gm_map {
     // streams queued them
     hipEvent_t added = nullptr;
     // recorded after the points' horizons, computed by the first launch that they pay for;
-    // later launches (on any stream) wait for it
+    // later launches (on any stream) wait for it until one finds it complete
     hipEvent_t horizon = nullptr;
+    bool horizon_done = false;
+    bool late_normals = false;  // the horizons brought the normals with them (no closed mesh)
     ~gm_map()
     {
         if (added) (void)hipEventDestroy(added);
@@ -138,20 +140,59 @@ gm_status check_map(const gm_map* m)
     return GM_OK;
 }
 
-// the horizons of a plain map's points, before a launch over F records on s
-gm_status map_horizon(gm_map* m, int64_t F, hipStream_t s)
+// The horizons of a plain map's points, before a launch over F records on s.  ready: the launch
+// may read them, where the map has them.  A graph cannot wait for an event from outside its
+// capture, so a launch that is being captured takes only horizons that are known to be
+// complete, and computes none (they would be there after a replay, not after the capture).
+gm_status map_horizon(gm_map* m, int64_t F, hipStream_t s, bool& ready)
 {
+    ready = true;
     if (m->w.horizon) {
-        GM_HIP(hipStreamWaitEvent(s, m->horizon, 0));
+        if (m->horizon_done) return GM_OK;
+        const bool captured = stream_captures(s);
+        if (!captured) GM_HIP(hipStreamWaitEvent(s, m->horizon, 0));
+        // the query is of finished work, also for a thread that is capturing
+        hipStreamCaptureMode cm = hipStreamCaptureModeRelaxed;
+        GM_HIP(hipThreadExchangeStreamCaptureMode(&cm));
+        m->horizon_done = hipEventQuery(m->horizon) == hipSuccess;
+        if (!m->horizon_done) (void)hipGetLastError();
+        GM_HIP(hipThreadExchangeStreamCaptureMode(&cm));
+        ready = m->horizon_done || !captured;
         return GM_OK;
     }
-    if (m->n <= 0 || !horizon_pays(m->n, F, m->sigma, m->mode) || !horizon_room(m->w, m->n, s)) return GM_OK;
+    if (m->n <= 0 || !horizon_pays(m->n, F, m->sigma, m->mode) || stream_captures(s) || !horizon_room(m->w, m->n, s))
+        return GM_OK;
     gm_status st = GM_OK;
-    if (!m->w.backface) st = density_backface(m->scene, m->w, m->n, m->mode, true, s);
+    if (!m->w.backface) {
+        st = density_backface(m->scene, m->w, m->n, m->mode, true, s);
+        m->late_normals = true;
+    }
     if (st == GM_OK && !m->horizon) GM_HIP(hipEventCreateWithFlags(&m->horizon, hipEventDisableTiming));
     if (st == GM_OK) st = density_horizon(m->scene, m->w, m->n, s);
     if (st == GM_OK) GM_HIP(hipEventRecord(m->horizon, s));
     return st;
+}
+
+// the launch of F records in `fix` (live of them) over a plain map's points
+gm_status map_launch(gm_map* m, int64_t F, const FixRec* fix, hipStream_t s)
+{
+    bool ready;
+    gm_status st = map_horizon(m, F, s, ready);
+    if (st != GM_OK) return st;
+    DensityLaunch a;
+    density_args(m->scene, m->w, m->n, (int32_t)F, m->sigma, m->mode, m->spl, 0, a);
+    if (!ready) {
+        a.hz = nullptr;
+        if (m->late_normals) {
+            a.bface = nullptr;
+            a.solid = nullptr;
+        }
+    }
+    a.fix = fix;
+    a.F_live = m->live.as<unsigned int>();
+    zero(m->w.stats.p, 8 * kDensityStats, s);
+    launch_density(a, s);
+    return GM_OK;
 }
 
 // one density launch over the pending records of a plain map
@@ -160,14 +201,8 @@ gm_status map_flush(gm_map* m, hipStream_t s)
     if (m->pending_hi == 0) return GM_OK;
     GM_HIP(hipStreamWaitEvent(s, m->added, 0));
     if (m->n > 0) {
-        gm_status st = map_horizon(m, m->pending_hi, s);
+        const gm_status st = map_launch(m, m->pending_hi, m->pending.as<FixRec>(), s);
         if (st != GM_OK) return st;
-        DensityLaunch a;
-        density_args(m->scene, m->w, m->n, (int32_t)m->pending_hi, m->sigma, m->mode, m->spl, 0, a);
-        a.fix = m->pending.as<FixRec>();
-        a.F_live = m->live.as<unsigned int>();
-        zero(m->w.stats.p, 8 * kDensityStats, s);
-        launch_density(a, s);
     }
     zero(m->live.p, 4, s);
     m->pending_hi = 0;
@@ -347,13 +382,8 @@ gm_status gm_map_add(gm_map* m, const gm_fixations* fix, const double* time, dou
         launch_fix_select(fix->eye, fix->gaze, fix->duration, time, F, t_begin, t_end, m->sigma, kGateWiden,
                           m->w.fix.as<FixRec>(), m->live.as<unsigned int>(), c, c + 2, s);
         if (m->n > 0) {
-            st = map_horizon(m, F, s);
+            st = map_launch(m, F, m->w.fix.as<FixRec>(), s);
             if (st != GM_OK) return st;
-            DensityLaunch a;
-            density_args(m->scene, m->w, m->n, F, m->sigma, m->mode, m->spl, 0, a);
-            a.F_live = m->live.as<unsigned int>();
-            zero(m->w.stats.p, 8 * kDensityStats, s);
-            launch_density(a, s);
         }
         zero(m->live.p, 4, s);
         GM_HIP(hipGetLastError());
