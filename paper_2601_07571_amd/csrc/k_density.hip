@@ -161,11 +161,9 @@ struct Seg {
 
 constexpr float kTlo = (float)kEpsV;  // t of the segment's point end at which occluders start
 
-// The slab tests' inverse: the hardware reciprocal (one unit in the last place; the boxes'
-// padding is over ten times what that moves a slab), a tenth of the instructions of a division.
 __device__ __forceinline__ float safe_inv(float d)
 {
-    return fabsf(d) > 1e-30f ? __builtin_amdgcn_rcpf(d) : copysignf(1e30f, d);
+    return fabsf(d) > 1e-30f ? 1.0f / d : copysignf(1e30f, d);
 }
 
 __device__ __forceinline__ float pick(int k, float a, float b, float c) { return k == 0 ? a : (k == 1 ? b : c); }
