@@ -109,11 +109,11 @@ gm_status infer_routed(gm_field* f, const float* pos, int64_t q, float* out, con
 // scratch of training over `batch` points and M networks
 gm_status train_scratch(gm_field* f, int32_t batch, int32_t M, FieldTrain& t)
 {
-    size_t buf, sums, se;
-    field_train_bytes(batch, M, buf, sums, se);
+    size_t buf, sums, part, se;
+    field_train_bytes(batch, M, buf, sums, part, se);
     GM_HIP(f->tbuf.ensure(buf));
     GM_HIP(f->tsums.ensure(sums));
-    GM_HIP(f->tpart.ensure(sums));
+    GM_HIP(f->tpart.ensure(part));
     GM_HIP(f->tse.ensure(se));
     t.buf = f->tbuf.as<unsigned char>();
     t.sums = f->tsums.as<float>();

@@ -335,9 +335,9 @@ struct FieldTrain {
     uint32_t key0, key1;     // Philox key of the batch draw
     uint32_t step;
     unsigned char* buf;      // activations and dZ of one pass's tiles (field_train_bytes)
-    float* sums;             // [networks][8][kFieldParams] row sums of the gradient
-    float* part;             // the same size: the slot in progress between passes
-    float* se;               // [networks][tiles] squared errors
+    float* sums;             // [networks at a time][rows][kFieldParams] row sums of the gradient
+    float* part;             // the same size, where needed: the slot in progress between passes
+    float* se;               // [networks at a time][tiles] squared errors
 };
 
 // Several networks in one launch (blockIdx.y = network): geometry, and the start and
@@ -348,6 +348,7 @@ struct FieldNets {
     const int64_t* off = nullptr;
     const int64_t* cnt = nullptr;
     int64_t pack_stride = 0;
+    int32_t first = 0;  // number of the launch's first network (its draw's key)
 };
 
 // the packed images of M networks (parameters kFieldParams apart, images field_pack_bytes() apart)
@@ -378,8 +379,8 @@ void launch_field_infer_routed(const unsigned char* blobs, int64_t pack_stride, 
 // sel[i] = flag[i] && mesh[i] == m
 void launch_field_select(const uint32_t* flag, const int32_t* mesh, int32_t m, int64_t n, uint32_t* sel, hipStream_t s);
 // Scratch of a training step or gradient over `batch` points and M networks: bytes of
-// FieldTrain::buf, sums (and part) and se.
-void field_train_bytes(int32_t batch, int32_t M, size_t& buf, size_t& sums, size_t& se);
+// FieldTrain::buf, sums, part and se.
+void field_train_bytes(int32_t batch, int32_t M, size_t& buf, size_t& sums, size_t& part, size_t& se);
 // The gradient grad [kFieldParams] and sum of squared errors loss [1] of one network over the
 // first t.batch points (or a drawn batch), every sum in an order fixed by the batch.
 void launch_field_gradient(const unsigned char* blob, const FieldGeom& g, const FieldTrain& t, float* grad, double* loss,

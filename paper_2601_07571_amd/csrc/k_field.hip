@@ -557,9 +557,9 @@ constexpr int kAux = 4 * kW + kW + 1;
 constexpr int kTileBytes = kOffAux + (kAux + 3) / 4 * 16;
 
 // row r, position q of a network: the tile, or -1; positions run through the row's slots,
-// `rounds` tiles each
+// `rounds` tiles each; rows: those that hold slots
 struct TileOrder {
-    int32_t tiles, slots, used, per, rounds;
+    int32_t tiles, slots, used, per, rounds, rows;
 };
 
 __device__ __forceinline__ int tile_at(const TileOrder& o, int r, int q)
@@ -615,7 +615,7 @@ __global__ void __launch_bounds__(64 * kTileWaves) k_field_tiles(const unsigned 
         g = nets.geom[net];
         t.idx += nets.off[net];
         t.n_idx = c;
-        t.key0 ^= (uint32_t)net;
+        t.key0 ^= (uint32_t)(nets.first + net);
     }
     __shared__ __attribute__((aligned(16))) unsigned char s_blob[kPack];
     __shared__ __attribute__((aligned(16))) __bf16 s_tr[kTileWaves][kW][kTileStride];
@@ -624,10 +624,10 @@ __global__ void __launch_bounds__(64 * kTileWaves) k_field_tiles(const unsigned 
     const int lane = __lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 31, h = lane >> 5;
     const int b = blockIdx.x * kTileWaves + wave;  // row-major over (row, position)
-    if (b >= kRows * Q) return;
+    if (b >= ord.rows * Q) return;
     const int tile = tile_at(ord, b / Q, q0 + b % Q);
     if (tile < 0) return;
-    unsigned char* out = buf + ((int64_t)net * kRows * Q + b) * kTileBytes;
+    unsigned char* out = buf + ((int64_t)net * ord.rows * Q + b) * kTileBytes;
     float* aux = reinterpret_cast<float*>(out + kOffAux);
     __bf16(*tr)[kTileStride] = s_tr[wave];
     const float* w5 = reinterpret_cast<const float*>(s_blob + kOffW5);
@@ -751,7 +751,7 @@ __global__ void __launch_bounds__(64 * kTileWaves) k_field_tiles(const unsigned 
 }
 
 // Row sums of the gradients over positions [q0, q0 + Q) of every row, continuing from
-// sums / part (the slot in progress) when q0 > 0: the two halves of layers 1..4's outputs in
+// sums / part (the slot in progress; NULL: one pass or one tile a slot) when q0 > 0: the two halves of layers 1..4's outputs in
 // blockIdx.z 0..7 (a wave per 32 of the layer's inputs), the biases and the output layer in 8
 // and 9.
 constexpr int kDwThreads = 192;
@@ -762,9 +762,9 @@ __global__ void __launch_bounds__(kDwThreads) k_field_dw(const unsigned char* __
 {
     const int r = blockIdx.x, net = blockIdx.y, layer = blockIdx.z >> 1, mb = blockIdx.z & 1;
     if (cnt && cnt[net] == 0) return;
-    const unsigned char* tiles = buf + ((int64_t)net * kRows + r) * Q * kTileBytes;
-    sums += ((int64_t)net * kRows + r) * kFieldParams;
-    part += ((int64_t)net * kRows + r) * kFieldParams;
+    const unsigned char* tiles = buf + ((int64_t)net * ord.rows + r) * Q * kTileBytes;
+    sums += ((int64_t)net * ord.rows + r) * kFieldParams;
+    if (part) part += ((int64_t)net * ord.rows + r) * kFieldParams;
     const int lane = __lane_id(), wave = threadIdx.x >> 6;
     // positions of this pass in the row, where a slot is one tile
     const int m = max(0, min(Q, min(ord.used, (r + 1) * ord.per) - r * ord.per - q0));
@@ -774,7 +774,7 @@ __global__ void __launch_bounds__(kDwThreads) k_field_dw(const unsigned char* __
         const int to = p < kW       ? kFieldOffB[1] + p
                        : p < 4 * kW ? kFieldOffB[2] + (p / kW - 1) * (kFieldOffB[3] - kFieldOffB[2]) + p % kW
                                     : kFieldOffW5 + p - 4 * kW;
-        float sum = q0 > 0 ? sums[to] : 0.0f, v = q0 > 0 ? part[to] : 0.0f;
+        float sum = q0 > 0 ? sums[to] : 0.0f, v = q0 > 0 && part ? part[to] : 0.0f;
         const float* src = reinterpret_cast<const float*>(tiles + kOffAux) + p;
         if (ord.rounds == 1) {
             int q = 0;
@@ -797,7 +797,7 @@ __global__ void __launch_bounds__(kDwThreads) k_field_dw(const unsigned char* __
             if (tile_at(ord, r, q0 + q + 1) < 0 || (q0 + q + 1) % ord.rounds == 0) sum += v;
         }
         sums[to] = sum;
-        part[to] = v;
+        if (part) part[to] = v;
         return;
     }
     const int nk = layer == 0 ? 3 : 2;
@@ -814,7 +814,7 @@ __global__ void __launch_bounds__(kDwThreads) k_field_dw(const unsigned char* __
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
             sum[k] = sums[to + 8 * (k >> 2) + (k & 3)];
-            v[k] = part[to + 8 * (k >> 2) + (k & 3)];
+            if (part) v[k] = part[to + 8 * (k >> 2) + (k & 3)];
         }
     }
     if (ord.rounds == 1) {
@@ -868,17 +868,17 @@ __global__ void __launch_bounds__(kDwThreads) k_field_dw(const unsigned char* __
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
         sums[to + 8 * (k >> 2) + (k & 3)] = sum[k];
-        if (ord.rounds > 1) part[to + 8 * (k >> 2) + (k & 3)] = v[k];
+        if (part) part[to + 8 * (k >> 2) + (k & 3)] = v[k];
     }
 }
 
-// the rows of a parameter in row order (networks with no training points: 0)
-__device__ __forceinline__ float row_total(const float* __restrict__ sums, int net, int p)
+// the rows of a parameter in row order (0 for a row without slots)
+__device__ __forceinline__ float row_total(const float* __restrict__ sums, int rows, int net, int p)
 {
-    const float* s = sums + (int64_t)net * kRows * kFieldParams + p;
+    const float* s = sums + (int64_t)net * rows * kFieldParams + p;
     float v[kRows];
 #pragma unroll
-    for (int r = 0; r < kRows; ++r) v[r] = s[(int64_t)r * kFieldParams];
+    for (int r = 0; r < kRows; ++r) v[r] = r < rows ? s[(int64_t)r * kFieldParams] : 0.0f;
     float g = v[0];
 #pragma unroll
     for (int r = 1; r < kRows; ++r) g += v[r];
@@ -909,7 +909,7 @@ __global__ void __launch_bounds__(kThreads) k_field_grad(const float* __restrict
                                                          float* __restrict__ grad, double* __restrict__ loss)
 {
     const int p = blockIdx.x * kThreads + threadIdx.x;
-    if (p < kFieldParams) grad[p] = row_total(sums, 0, p);
+    if (p < kFieldParams) grad[p] = row_total(sums, ord.rows, 0, p);
     if (blockIdx.x == 0) total_loss(se, ord, true, loss);
 }
 
@@ -971,7 +971,7 @@ __global__ void __launch_bounds__(kThreads) k_field_step(const float* __restrict
     if (p < kFieldParams) {
         const int64_t i = (int64_t)net * kFieldParams + p;
         float x = master[i], m = m1[i], v = m2[i];
-        const float g = live ? row_total(sums, net, p) : 0.0f;
+        const float g = live ? row_total(sums, ord.rows, net, p) : 0.0f;
         x = adam(x, m, v, g, a);
         master[i] = x;
         m1[i] = m;
@@ -1200,38 +1200,58 @@ TileOrder tile_order(int32_t batch, int32_t M)
     o.used = std::min(o.tiles, o.slots);
     o.per = (o.used + kRows - 1) / kRows;
     o.rounds = (o.tiles + o.slots - 1) / o.slots;
+    o.rows = (o.used + o.per - 1) / o.per;
     return o;
 }
 
-// positions of a row that one pass of the two kernels takes: all of them up to 8,192 tiles
-// (285 MB) over the networks, else that many
-int32_t pass_positions(const TileOrder& o, int32_t M)
+// How a step is cut: `nets` networks at a time, `positions` of each of their rows in a pass of the
+// two kernels, so that a pass holds at most 8,192 tiles (285 MB) and 2,048 rows (154 MB of sums),
+// or one position of one network's rows.  Whole networks come first: cut by positions alone, a
+// pass of many networks holds a few tiles of each, and each stages its 70 KB image for them.  A
+// step of 30 networks x 16,384 points 0.47 -> 0.42 ms, 300 x 1,024 0.98 -> 0.46, 1,000 x 256 2.72
+// -> 0.67, 1,000 x 16,384 170 -> 13.7 (with 1.5 GB -> 0.3 GB of scratch).
+struct TrainCut {
+    int32_t nets, positions;
+    int64_t all;  // positions of a row
+    bool parts;   // a slot may be cut by a pass
+};
+
+TrainCut train_cut(const TileOrder& o, int32_t M)
 {
-    const int64_t all = (int64_t)o.per * o.rounds;
-    return (int32_t)std::min<int64_t>(all, std::max<int64_t>(1, 8192 / ((int64_t)kRows * M)));
+    constexpr int64_t kPassTiles = 8192, kPassRows = 2048;
+    TrainCut c;
+    c.all = (int64_t)o.per * o.rounds;
+    const int64_t most = std::min(kPassTiles / std::max<int64_t>(1, c.all * o.rows), kPassRows / o.rows);
+    const int64_t groups = most > 0 ? (M + most - 1) / most : M;
+    c.nets = (int32_t)((M + groups - 1) / groups);
+    c.positions = (int32_t)std::min<int64_t>(c.all, std::max<int64_t>(1, kPassTiles / ((int64_t)o.rows * c.nets)));
+    c.parts = c.positions < c.all && o.rounds > 1;
+    return c;
 }
 
-// row sums of one step over every network
+// row sums of one step over M <= cut.nets networks
 void launch_field_sums(const unsigned char* blob, const FieldGeom& g, const FieldTrain& t, const FieldNets& nets, int32_t M,
-                       const TileOrder& o, hipStream_t s)
+                       const TileOrder& o, const TrainCut& c, hipStream_t s)
 {
-    const int Q = pass_positions(o, M);
-    const int64_t all = (int64_t)o.per * o.rounds;
-    for (int64_t q0 = 0; q0 < all; q0 += Q) {
-        const dim3 grid((unsigned)((kRows * Q + kTileWaves - 1) / kTileWaves), (unsigned)M);
+    const int Q = c.positions;
+    for (int64_t q0 = 0; q0 < c.all; q0 += Q) {
+        const dim3 grid((unsigned)((o.rows * Q + kTileWaves - 1) / kTileWaves), (unsigned)M);
         k_field_tiles<<<grid, 64 * kTileWaves, 0, s>>>(blob, g, t, nets, o, (int)q0, Q, t.buf);
-        k_field_dw<<<dim3(kRows, (unsigned)M, 10), kDwThreads, 0, s>>>(t.buf, nets.cnt, o, (int)q0, Q, t.sums, t.part);
+        k_field_dw<<<dim3((unsigned)o.rows, (unsigned)M, 10), kDwThreads, 0, s>>>(t.buf, nets.cnt, o, (int)q0, Q, t.sums,
+                                                                                  c.parts ? t.part : nullptr);
     }
 }
 
 }  // namespace
 
-void field_train_bytes(int32_t batch, int32_t M, size_t& buf, size_t& sums, size_t& se)
+void field_train_bytes(int32_t batch, int32_t M, size_t& buf, size_t& sums, size_t& part, size_t& se)
 {
     const TileOrder o = tile_order(batch, M);
-    buf = (size_t)M * kRows * (size_t)pass_positions(o, M) * kTileBytes;
-    sums = (size_t)M * kRows * kFieldParams * sizeof(float);
-    se = (size_t)M * (size_t)o.tiles * sizeof(float);
+    const TrainCut c = train_cut(o, M);
+    buf = (size_t)c.nets * (size_t)o.rows * (size_t)c.positions * kTileBytes;
+    sums = (size_t)c.nets * (size_t)o.rows * kFieldParams * sizeof(float);
+    part = c.parts ? sums : 0;
+    se = (size_t)c.nets * (size_t)o.tiles * sizeof(float);
 }
 
 void launch_field_gradient(const unsigned char* blob, const FieldGeom& g, const FieldTrain& t, float* grad, double* loss,
@@ -1239,7 +1259,7 @@ void launch_field_gradient(const unsigned char* blob, const FieldGeom& g, const 
 {
     if (t.batch <= 0) return;
     const TileOrder o = tile_order(t.batch, 1);
-    launch_field_sums(blob, g, t, FieldNets{}, 1, o, s);
+    launch_field_sums(blob, g, t, FieldNets{}, 1, o, train_cut(o, 1), s);
     k_field_grad<<<blocks(kFieldParams), kThreads, 0, s>>>(t.sums, t.se, o, grad, loss);
 }
 
@@ -1248,9 +1268,21 @@ void launch_field_step(unsigned char* blob, const FieldNets& nets, int32_t M, co
 {
     if (t.batch <= 0 || M <= 0) return;
     const TileOrder o = tile_order(t.batch, M);
-    launch_field_sums(blob, FieldGeom{}, t, nets, M, o, s);
-    k_field_step<<<dim3(blocks(kFieldParams), (unsigned)M), kThreads, 0, s>>>(t.sums, t.se, nets.cnt, o, AdamStep{lr, b1, b2, eps, c1, c2},
-                                                                            master, m, v, blob, nets.pack_stride, loss);
+    const TrainCut c = train_cut(o, M);
+    for (int32_t n0 = 0; n0 < M; n0 += c.nets) {
+        const int32_t n = std::min(c.nets, M - n0);
+        const int64_t p0 = (int64_t)n0 * kFieldParams;
+        FieldNets some = nets;
+        some.geom += n0;
+        some.off += n0;
+        some.cnt += n0;
+        some.first = n0;
+        unsigned char* image = blob + (int64_t)n0 * nets.pack_stride;
+        launch_field_sums(image, FieldGeom{}, t, some, n, o, c, s);
+        k_field_step<<<dim3(blocks(kFieldParams), (unsigned)n), kThreads, 0, s>>>(
+            t.sums, t.se, some.cnt, o, AdamStep{lr, b1, b2, eps, c1, c2}, master + p0, m + p0, v + p0, image,
+            nets.pack_stride, loss + n0);
+    }
 }
 
 void launch_field_adam(float* master, float* m, float* v, float* grad, int64_t count, float lr, float b1, float b2,
