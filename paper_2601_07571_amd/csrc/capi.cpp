@@ -350,7 +350,7 @@ gm_status density_backface(gm_scene* sc, DensityWork& w, int64_t n, uint32_t mod
     w.backface = false;
     if (mode == GM_OCC_NONE || (!sc->any_closed() && !normals) || n <= 0) return GM_OK;
     GM_HIP(w.bface.ensure(16 * (size_t)(off + n)));
-    GM_HIP(w.bcand.ensure(4 * (size_t)kBfCand * (size_t)(off + n)));
+    GM_HIP(w.bcand.ensure(backface_list_bytes(sc, off + n)));
     launch_backface_prep(w.spos.as<float4>() + off, w.smesh.as<int32_t>() + off, n, sc->V.as<float>(),
                          sc->I.as<int32_t>(), sc->closed_d.as<uint8_t>(), sc->M, sc->nodes.as<BvhNode>(),
                          sc->tris.as<BvhTri>() + 2 * sc->bvh.tris.size(), sc->bf_rmax, sc->solid_near,
@@ -369,9 +369,16 @@ bool stream_captures(hipStream_t s)
     return true;
 }
 
-bool horizon_room(DensityWork& w, int64_t n, hipStream_t s)
+size_t backface_list_bytes(const gm_scene* sc, int64_t n)
 {
-    const size_t bf = 16 * (size_t)n, bc = 4 * (size_t)kBfCand * (size_t)n, hz = 4 * (size_t)n;
+    for (uint8_t c : sc->closed_topology)
+        if (c) return 4 * (size_t)kBfCand * (size_t)n;
+    return 0;
+}
+
+bool horizon_room(const gm_scene* sc, DensityWork& w, int64_t n, hipStream_t s)
+{
+    const size_t bf = 16 * (size_t)n, bc = backface_list_bytes(sc, n), hz = 4 * (size_t)n;
     if (w.bface.bytes >= bf && w.bcand.bytes >= bc && w.hz.bytes >= hz) return true;
     if (!stream_captures(s) && w.bface.ensure(bf) == hipSuccess && w.bcand.ensure(bc) == hipSuccess &&
         w.hz.ensure(hz) == hipSuccess)
@@ -427,7 +434,7 @@ gm_status density_prep(gm_scene* sc, DensityWork& w, const float* pos, const int
     begin.buckets = w.buckets;
     launch_map_begin(begin, sigma, kGateWiden, s);
     density_sort(sc, w, pos, tri, mesh, n, s, 0, true);
-    const bool horizon = n > 0 && horizon_pays(n, F, sigma, mode) && horizon_room(w, n, s);
+    const bool horizon = n > 0 && horizon_pays(n, F, sigma, mode) && horizon_room(sc, w, n, s);
     w.horizon = false;
     gm_status st = density_backface(sc, w, n, mode, horizon, s);
     if (st == GM_OK && horizon) st = density_horizon(sc, w, n, s);

@@ -240,13 +240,16 @@ gm_status density_prep(gm_scene* sc, DensityWork& w, const float* pos, const int
 // (normals: also without a closed mesh, for the horizon rule)
 gm_status density_backface(gm_scene* sc, DensityWork& w, int64_t n, uint32_t mode, bool normals, hipStream_t s,
                            int64_t off = 0);
+// bytes of n points' back-face lists: none in a scene without a mesh whose flag can be set (its
+// points get normals alone, for their horizons)
+size_t backface_list_bytes(const gm_scene* sc, int64_t n);
 // whether the horizons of n points pay for themselves over F fixations
 bool horizon_pays(int64_t n, int64_t F, double sigma, uint32_t mode);
 // whether s is being captured (or cannot say)
 bool stream_captures(hipStream_t s);
 // whether w holds (or can be given) the buffers of n points' horizons: without them, as in a
 // capture that would have to allocate, the rule is left out
-bool horizon_room(DensityWork& w, int64_t n, hipStream_t s);
+bool horizon_room(const gm_scene* sc, DensityWork& w, int64_t n, hipStream_t s);
 // the horizons of the n sorted points of w, whose normals density_backface has written
 gm_status density_horizon(gm_scene* sc, DensityWork& w, int64_t n, hipStream_t s);
 // squared length of the longest segment the rule takes (see DensityLaunch::bf_L2max)
