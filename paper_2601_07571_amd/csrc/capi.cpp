@@ -70,14 +70,27 @@ void zero(void* p, size_t bytes, hipStream_t s) { fill_u32(p, (int64_t)((bytes +
 
 namespace {
 
-// Boxes per closed mesh: kSolidScene over the scene's closed meshes, within these bounds.
-// More boxes settle more occluded pairs but each packet walks their tree.  Density kernel at
-// 1 / 3 / 6 / 10 / 16 / 48 boxes a mesh: three objects and a terrain, 2M samples x 6,000
-// fixations, 29.1 / 28.0 / 27.3 / 26.9 / 27.0 / 27.9 ms (36.7 without); 25 spheres, 400,003 x
-// 12,000, 13.9 / 13.3 / 13.3 / 13.5 / 14.2 / 15.7 ms (17.0 without).
+// Boxes per closed mesh: kSolidScene over the meshes that have any, within kSolidLeast and
+// kSolidMost, and at most one for every kSolidPer triangles of the mesh or its share of one for
+// every kSolidShare triangles of the scene, whichever is more (so their tree stays a thousandth of
+// the scene's).  More boxes settle more occluded pairs but each packet walks their tree.  Map time
+// at 0 / 1 / 4 / 10 / 16 / 48 boxes a mesh: three objects and a terrain, 2M samples x 6,000
+// fixations, 25.6 / 25.3 / 24.9 / 25.2 / 25.2 / 26.0 ms; 25 spheres of 20,000 triangles, 400,003 x
+// 12,000, 18.2 / 14.8 / 14.1 / 14.3 / 14.6 / 16.2 ms.
+// A mesh of fewer than kSolidPer triangles is so shallow a tree that walking its boxes costs as
+// much as the descents they save.  150,000 samples x 1,500 fixations, 144 spheres of 320 / 720 /
+// 1,280 / 5,120 triangles, 0.35 of their spacing wide: 1.00 / 1.24 / 1.43 / 2.12 ms with one box
+// each, 0.94 / 1.20 / 1.41 / 2.21 without; 0.7 wide: 1.16 / 1.35 / 1.57 / 2.31 and 1.17 / 1.43 / 1.72
+// / 2.74; 2,304 of 180 triangles: 2.52 and 2.81 with, 2.22 and 2.69 without.  But a coarse mesh
+// among fine ones is worth its boxes: the objects (one is a cube) take 1 to 5 % longer when the
+// cube has none.
+// Self occlusion has none: what a point's own boxes could settle, the back-face rule has settled
+// (the triangle tests stay the same); 100 spheres of 8,000 triangles 10.24 ms with, 9.87 without.
 constexpr int kSolidLeast = 4;
 constexpr int kSolidMost = 12;
 constexpr int kSolidScene = 128;
+constexpr int64_t kSolidPer = 1000;
+constexpr int64_t kSolidShare = 20000;
 
 // a1 + a2 on the device, once per scene: areas, weights, their scan and the per-mesh
 // totals and scale exponents, the last two read back to the host (blocking, once).
@@ -329,7 +342,7 @@ void density_args(const gm_scene* sc, const DensityWork& w, int64_t n, int32_t F
             a.hz = w.hz.as<float>();
             a.hz_reach = sc->hz_reach;
         }
-        if (sc->solid_n > 0 && sc->any_closed()) {
+        if (mode == GM_OCC_FULL && sc->solid_n > 0 && sc->any_closed()) {
             a.solid = sc->solid.as<BvhNode>();
             a.solid_stride = sc->solid_n;
             a.solid_mbox = sc->solid_mbox_d.as<float4>();
@@ -559,14 +572,20 @@ gm_status gm_scene_create(const gm_mesh* meshes, int32_t n_meshes, gm_scene** ou
         for (int c = 0; c < 3; ++c)
             scale = std::max(scale, std::max(std::fabs((double)sc->bvh.lo[c]), std::fabs((double)sc->bvh.hi[c])));
         int32_t n_closed = 0;
-        for (uint8_t c : sc->closed) n_closed += c;
-        const int most = std::max(kSolidLeast, std::min(kSolidMost, kSolidScene / std::max(1, n_closed)));
+        for (uint8_t f : sc->closed) n_closed += f;
+        const int64_t share = T / (kSolidShare * std::max(1, n_closed));
+        auto boxes_of = [&](int32_t m) -> int64_t {
+            const int64_t t = meshes[m].n_triangles;
+            return sc->closed[(size_t)m] ? std::max(share, t / kSolidPer) : 0;
+        };
+        int32_t n_solid = 0;
+        for (int32_t m = 0; m < n_meshes; ++m) n_solid += boxes_of(m) > 0;
+        const int64_t most = std::max(kSolidLeast, std::min(kSolidMost, kSolidScene / std::max(1, n_solid)));
         double near = INFINITY;
         std::vector<SolidBox> boxes;
         for (int32_t m = 0; m < n_meshes; ++m)
-            if (sc->closed[(size_t)m])
-                near = std::min(near, solid_boxes(meshes[m].vertices, meshes[m].indices, meshes[m].n_triangles, scale,
-                                                  most, m, boxes));
+            near = std::min(near, solid_boxes(meshes[m].vertices, meshes[m].indices, meshes[m].n_triangles, scale,
+                                              (int)std::min(most, boxes_of(m)), m, boxes));
         sc->solid_near = (float)(0.5 * near);
         std::vector<BvhNode> nodes;
         build_solid_tree(std::move(boxes), nodes);
@@ -832,7 +851,7 @@ gm_status gm_debug_pair_visibility(gm_scene* sc, const float* pos, const int32_t
         bf.rmax = sc->bf_rmax;
         bf.l2max = backface_l2max(sc);
         bf.near = sc->solid_near;
-        if (sc->solid_n > 0) bf.solid = sc->solid.as<BvhNode>();
+        if (mode == GM_OCC_FULL && sc->solid_n > 0) bf.solid = sc->solid.as<BvhNode>();
         bf.solid_mbox = sc->solid_mbox_d.as<float4>();
     }
     launch_pair_visibility(pos, tri, mesh, sc->tri_mesh.as<int32_t>(), eye, gaze, pair_s, pair_f, m, n_points, n_eyes,

@@ -492,15 +492,15 @@ __device__ void occluded_packet(const BvhNode* __restrict__ nodes, const BvhTri*
 // (a convex set) is nowhere larger than at its start.  So the rule is for points within
 // solid_near of their triangle (half the least distance of a box), or without one.  mbox: those
 // bounding boxes, unbounded for a mesh whose closed flag is cleared.  The packet walks
-// the tree over the solid boxes (a few hundred at most: it stays in the scalar cache) as
+// the tree over the solid boxes (one for a thousand triangles at most) as
 // occluded_packet walks the triangles'; a lane is done at its first box.  An occluded
 // packet then costs a few node visits instead of a descent to the triangles.
 // Returns the lanes of `live` that are occluded.
 // ---------------------------------------------------------------------------
 template <bool UNI>
 __device__ __forceinline__ uint64_t solid_packet(const BvhNode* __restrict__ nodes, const float4* __restrict__ mbox,
-                                                 int oct, const Seg& sg, float ex, float ey, float ez, int own_mesh,
-                                                 int mode, uint64_t live, TravCount& visits)
+                                                 int oct, const Seg& sg, float ex, float ey, float ez,
+                                                 uint64_t live, TravCount& visits)
 {
     const int lane = lane_id();
     uint64_t hit = 0;
@@ -522,7 +522,6 @@ __device__ __forceinline__ uint64_t solid_packet(const BvhNode* __restrict__ nod
                 const int m = ~child;
                 const float4 lo = mbox[2 * m], hi = mbox[2 * m + 1];
                 h &= ballot(ex < lo.x || ex > hi.x || ey < lo.y || ey > hi.y || ez < lo.z || ez > hi.z);
-                if (mode == 1) h &= ballot(own_mesh == m);
                 hit |= h;
                 live &= ~h;
             } else if (next < 0) {
@@ -1820,7 +1819,7 @@ __device__ __forceinline__ void packet_visibility(const BfArgs* bf, const BvhNod
 #pragma unroll
             for (int k = 0; k < SPL; ++k) {
                 solid[k] = __builtin_amdgcn_inverse_ballot_w64(
-                    solid_packet<true>(so, mb, oct, sg[k], ex, ey, ez, omesh[k], mode, ballot(need[k] && t0[k] > 0.0f), n_visits));
+                    solid_packet<true>(so, mb, oct, sg[k], ex, ey, ez, ballot(need[k] && t0[k] > 0.0f), n_visits));
                 need[k] = need[k] && !solid[k];
             }
         }
@@ -1843,7 +1842,7 @@ __device__ __forceinline__ void packet_visibility(const BfArgs* bf, const BvhNod
 #pragma unroll
             for (int k = 0; k < SPL; ++k) {
                 solid[k] = __builtin_amdgcn_inverse_ballot_w64(
-                    solid_packet<false>(sn, mb, oct, sg[k], ex, ey, ez, omesh[k], mode, ballot(need[k] && t0[k] > 0.0f), n_visits));
+                    solid_packet<false>(sn, mb, oct, sg[k], ex, ey, ez, ballot(need[k] && t0[k] > 0.0f), n_visits));
                 need[k] = need[k] && !solid[k];
             }
         }
@@ -2402,8 +2401,8 @@ __global__ void __launch_bounds__(64) k_pair_visibility(const float* __restrict_
             return;
         }
     }
-    if (bf.solid && mode != 0 && ballot(own) != 0 &&
-        solid_packet<false>(bf.solid, bf.solid_mbox, oct, sgs[0], ex, ey, ez, me, mode, 1ull, visits) != 0) {
+    if (bf.solid && ballot(own) != 0 &&
+        solid_packet<false>(bf.solid, bf.solid_mbox, oct, sgs[0], ex, ey, ez, 1ull, visits) != 0) {
         if (lane == 0) vis[i] = 0;
         return;
     }
