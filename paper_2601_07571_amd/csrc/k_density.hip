@@ -1172,6 +1172,7 @@ __device__ __forceinline__ Seg make_ray(float ex, float ey, float ez, float dx, 
     s.sx = pick(kx, dx, dy, dz) / dkz;
     s.sy = pick(ky, dx, dy, dz) / dkz;
     s.tz = dkz;
+    s.t0 = 0.0f;
     return s;
 }
 
