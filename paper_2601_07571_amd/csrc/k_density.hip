@@ -2218,7 +2218,12 @@ __device__ __forceinline__ void density_item(const DensityLaunch& a, int64_t til
 // Items in dispatch order go tile by tile, the chunks of one tile next to each other:
 // workgroups are handed out round-robin over the XCDs, so the chunks of a tile run at
 // once on different XCDs and every XCD sees every part of the scene; when only the
-// first chunks hold fixations (a time window), the work still spreads over all XCDs.
+// first chunks hold fixations (a time window), the work still spreads over all XCDs.  Where
+// the chunks are a multiple of 16, every tile's chunk c would run on the same few CUs, and chunks
+// differ in work: there each tile begins with another chunk, a hash of the tile (300,000 points
+// on a sphere of 20,480 triangles x 1,000 fixations in 16 / 31 / 32 / 33 chunks 1.53 / 1.47 / 1.88 /
+// 1.48 ms without, 1.40 / 1.47 / 1.47 / 1.48 with it).  For other numbers the plain order, in which
+// neighbouring tiles share their fixations, is the better one (2M points x 6,000: 1 %).
 // ZB: the paper's z-buffer visibility instead of the exact segment test.
 // Occupancy: the one-sample-per-lane traversal kernels (this one, k_density_queue and
 // k_zbuffer) ask for 8 waves per SIMD, the most the SIMD holds; their scalar registers
@@ -2234,7 +2239,9 @@ __global__ void __launch_bounds__(kThreads, (kMinWaves<SPL, OCC>)) k_density(Den
 {
     const unsigned L = blockIdx.x + blockIdx.y * gridDim.x;  // < 2^31 (tiles x chunks)
     const int F = a.F_live ? min(a.F, (int)*a.F_live) : a.F;
-    density_item<SPL, OCC, kFB, INST, ZB>(a, (int64_t)(L / gridDim.y), (int)(L % gridDim.y), F);
+    const unsigned tile = L / gridDim.y;
+    const unsigned turn = (gridDim.y & 15) == 0 ? (tile * 0x9E3779B1u) >> 16 : 0u;
+    density_item<SPL, OCC, kFB, INST, ZB>(a, (int64_t)tile, (int)((L - tile * gridDim.y + turn) % gridDim.y), F);
 }
 
 // Persistent form for many sessions: every workgroup pulls (session, tile, chunk)
