@@ -148,7 +148,7 @@ gm_status prepare(gm_batch* b, const TileConfig& cfg, hipStream_t s)
         const int64_t tiles_i = std::max<int64_t>(1, (ss.n + 256 * cfg.spl - 1) / (256 * cfg.spl));
         const int32_t chunk = cfg.chunk > 0
                                   ? cfg.chunk
-                                  : auto_fix_per_chunk(tiles_i, ss.fix.n, tile_fixations, ss.flags & GM_OCC_MASK);
+                                  : auto_fix_per_chunk(ss.scene, tiles_i, ss.fix.n, tile_fixations, ss.flags & GM_OCC_MASK);
         gm_status st = density_prep(ss.scene, *b->work[i], ss.pos, ss.tri, ss.mesh, ss.n, &ss.fix, ss.theta_deg,
                                     ss.flags & GM_OCC_MASK, cfg.spl, chunk, b->launches[i], s);
         if (st != GM_OK) return st;

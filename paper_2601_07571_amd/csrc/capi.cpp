@@ -278,7 +278,7 @@ void density_sort(gm_scene* sc, DensityWork& w, const float* pos, const int32_t*
                    w.inv.as<int32_t>() + off, (int32_t)off, s);
 }
 
-int32_t auto_fix_per_chunk(int64_t tiles, int32_t F, double tile_fixations, uint32_t mode)
+int32_t auto_fix_per_chunk(const gm_scene* sc, int64_t tiles, int32_t F, double tile_fixations, uint32_t mode)
 {
     // The cost of a (tile, chunk) item varies a lot (how many of its fixations see the tile),
     // so a large grid holds many small items: at least ~512k of them and at most 1024
@@ -297,9 +297,15 @@ int32_t auto_fix_per_chunk(int64_t tiles, int32_t F, double tile_fixations, uint
     // (60,000 triangles) 242 / 275 / 364 / 382; 59 x 100 in a room 250 / 256 / 316 / 379; 196 x
     // 100 340 / 352 / 417 / 421.  Without: 40 x 1,000 157 / 110 / 82 / 78 / 92 / 132 us; 391 x
     // 3,000 2.17 / 1.48 / 0.93 / 0.56 / 0.33 / 0.27 ms (0.32 at 256, 0.46 at 512).
+    // Those with occlusion are of scenes of 60,000 triangles and more; in a shallow tree or a
+    // flat scene a pair costs little more than without, and the line lies between the two.  235
+    // tiles x 1,000 at 12 / 16 / 32 / 64 / 128: a cube (12 triangles) 305 / 242 / 182 / 174 / 179 us,
+    // spheres of 320 triangles 320 / 277 / 267 / 270 / 322, of 5,120 467 / 438 / 472 / 456 / 560, of
+    // 20,480 693 / 665 / 731 / 754 / 870; 1,172 x 1,000 at 27 / 64 / 128: a cube 638 / 520 / 481.
     const bool occ = mode != GM_OCC_NONE;
     const double root = std::sqrt(std::max(1.0, tile_fixations));
-    const int64_t min_chunk = std::min<int64_t>(occ ? 128 : 512, std::max<int64_t>(occ ? 1 : 16, (int64_t)(root / (occ ? 40.0 : 8.0))));
+    const double parts = occ ? std::min(40.0, 8.0 + 3.5 * sc->walk_levels) : 8.0;
+    const int64_t min_chunk = std::min<int64_t>(occ ? 128 : 512, std::max<int64_t>(occ ? 1 : 16, (int64_t)(root / parts)));
     const int64_t max_chunks = std::max<int64_t>(1, (F + min_chunk - 1) / min_chunk);
     const int64_t want = std::max<int64_t>((524288 + tiles - 1) / tiles, (F + 1023) / 1024);
     // the grid is tiles x chunks: chunks <= 65535 (grid y) and tiles x chunks < 2^31
@@ -328,7 +334,7 @@ void density_args(const gm_scene* sc, const DensityWork& w, int64_t n, int32_t F
     a.stats = w.stats.as<unsigned long long>();
     a.spl = spl;
     const int64_t tiles = std::max<int64_t>(1, (n + 256 * spl - 1) / (256 * spl));
-    if (fix_per_chunk <= 0) fix_per_chunk = auto_fix_per_chunk(tiles, F, (double)tiles * (double)F, mode);
+    if (fix_per_chunk <= 0) fix_per_chunk = auto_fix_per_chunk(sc, tiles, F, (double)tiles * (double)F, mode);
     a.fix_per_chunk = fix_per_chunk;
     a.n_chunks = F > 0 ? (int32_t)((F + fix_per_chunk - 1) / fix_per_chunk) : 0;
     a.F_live = nullptr;
@@ -400,7 +406,7 @@ bool horizon_room(const gm_scene* sc, DensityWork& w, int64_t n, hipStream_t s)
     return false;
 }
 
-bool horizon_pays(int64_t n, int64_t F, double sigma, uint32_t mode)
+bool horizon_pays(const gm_scene* sc, int64_t n, int64_t F, double sigma, uint32_t mode)
 {
     // A point's walked pairs grow with F sigma^2 (its share of the cones), its horizon costs
     // one walk of its neighbourhood.  Map time without / with: three objects and a terrain,
@@ -411,7 +417,13 @@ bool horizon_pays(int64_t n, int64_t F, double sigma, uint32_t mode)
     // 1,200 / 2,400 fixations at 1 degree (0.09 / 0.18 / 0.37 / 0.73) 509 / 551 / 784 / 1,244 us
     // without, 469 / 543 / 661 / 901 with; 25 spheres 520 / 714 / 832 / 1,122 and 568 / 593 /
     // 735 / 1,033; 120,000 points at 0.37 / 0.73 1,249 / 1,909 and 1,420 / 1,989.
-    return mode != GM_OCC_NONE && (double)F * sigma * sigma >= (n <= 65536 ? 0.2 : 1.0);
+    // Those are scenes of 60,000 triangles and more.  60,000 points at 0.3 / 3.0: spheres of 20,480
+    // triangles 693 / 3,987 without, 604 / 2,508 with; 5,120 467 / 2,559 and 493 / 1,754; 1,280 359 /
+    // 1,890 and 452 / 1,389; 80 317 / 1,375 and 385 / 1,108; a cube 305 / 1,108 and 384 / 1,208; a flat
+    // plate of 2,048 289 / 1,317 and 390 / 1,542.  The fewest triangles and flat scenes never pay:
+    // a segment leaves their boxes at once.
+    if (mode == GM_OCC_NONE || sc->walk_levels < 2.0) return false;
+    return (double)F * sigma * sigma >= (n <= 65536 && sc->T >= 8192 ? 0.2 : 1.0);
 }
 
 gm_status density_horizon(gm_scene* sc, DensityWork& w, int64_t n, hipStream_t s)
@@ -447,7 +459,7 @@ gm_status density_prep(gm_scene* sc, DensityWork& w, const float* pos, const int
     begin.buckets = w.buckets;
     launch_map_begin(begin, sigma, kGateWiden, s);
     density_sort(sc, w, pos, tri, mesh, n, s, 0, true);
-    const bool horizon = n > 0 && horizon_pays(n, F, sigma, mode) && horizon_room(sc, w, n, s);
+    const bool horizon = n > 0 && horizon_pays(sc, n, F, sigma, mode) && horizon_room(sc, w, n, s);
     w.horizon = false;
     gm_status st = density_backface(sc, w, n, mode, horizon, s);
     if (st == GM_OK && horizon) st = density_horizon(sc, w, n, s);
@@ -563,6 +575,15 @@ gm_status gm_scene_create(const gm_mesh* meshes, int32_t n_meshes, gm_scene** ou
         // 31.3 ms at 2 / 4 / 8 (its horizons 1.4 / 2.1 / 3.3 of them), a sphere of 12,007 x 2,501
         // 1.08 / 1.09 / 1.33
         sc->hz_reach = (float)(4.0 * sum / (3.0 * (double)T));
+    }
+    {
+        double least = INFINITY, most = 0.0;
+        for (int a = 0; a < 3; ++a) {
+            const double e = (double)sc->bvh.hi[a] - sc->bvh.lo[a];
+            least = std::min(least, e);
+            most = std::max(most, e);
+        }
+        sc->walk_levels = least <= 1e-3 * most ? 0.0 : std::max(0.0, std::log2((double)T / 16.0));
     }
     sc->closed_topology = sc->closed;
     sc->mbox = mbox;

@@ -177,6 +177,9 @@ struct gm_scene {
     std::vector<uint8_t> closed, closed_topology;
     DevBuf closed_d, mbox_d;
     float bf_rmax = 0.0f;
+    // levels of the tree above 16 triangles, about what a packet that meets nothing walks down; 0
+    // for a flat scene, whose boxes a segment leaves at once
+    double walk_levels = 0.0;
     float hz_reach = 0.0f;  // distance from a point within which its horizon holds every triangle
     // the tree over the boxes inside the meshes that gm_mesh_closed passed (octant copies;
     // solid_n nodes a copy, 0: none) and those meshes' bounding boxes as the boxes' rule reads
@@ -244,7 +247,7 @@ gm_status density_backface(gm_scene* sc, DensityWork& w, int64_t n, uint32_t mod
 // points get normals alone, for their horizons)
 size_t backface_list_bytes(const gm_scene* sc, int64_t n);
 // whether the horizons of n points pay for themselves over F fixations
-bool horizon_pays(int64_t n, int64_t F, double sigma, uint32_t mode);
+bool horizon_pays(const gm_scene* sc, int64_t n, int64_t F, double sigma, uint32_t mode);
 // whether s is being captured (or cannot say)
 bool stream_captures(hipStream_t s);
 // whether w holds (or can be given) the buffers of n points' horizons: without them, as in a
@@ -263,7 +266,7 @@ void density_args(const gm_scene* sc, const DensityWork& w, int64_t n, int32_t F
                   int spl, int32_t fix_per_chunk, DensityLaunch& a);
 // fixations per work item for one launch (or one session of a batch) of `tiles` tiles and F
 // fixations, when the whole launch holds tile_fixations (tile, fixation) pairs
-int32_t auto_fix_per_chunk(int64_t tiles, int32_t F, double tile_fixations, uint32_t mode);
+int32_t auto_fix_per_chunk(const gm_scene* sc, int64_t tiles, int32_t F, double tile_fixations, uint32_t mode);
 // maximum and outputs
 gm_status density_finalize(DensityWork& w, int64_t n, float* density, float* density_norm, float* max_out,
                            hipStream_t s);

@@ -160,7 +160,8 @@ gm_status map_horizon(gm_map* m, int64_t F, hipStream_t s, bool& ready)
         ready = m->horizon_done || !captured;
         return GM_OK;
     }
-    if (m->n <= 0 || !horizon_pays(m->n, F, m->sigma, m->mode) || stream_captures(s) || !horizon_room(m->scene, m->w, m->n, s))
+    if (m->n <= 0 || !horizon_pays(m->scene, m->n, F, m->sigma, m->mode) || stream_captures(s) ||
+        !horizon_room(m->scene, m->w, m->n, s))
         return GM_OK;
     gm_status st = GM_OK;
     if (!m->w.backface) {

@@ -12,14 +12,13 @@ pytestmark = pytest.mark.gpu
 def test_open_scene_holds_no_backface_lists():
     import torch
     import paper_2601_07571_amd as gm
-    plate = workloads.plate_mesh(size=1.0, cells=40)
-    scene = gm.Scene([(plate.V, plate.I)])
+    m = workloads.heightfield_mesh(fine=(64, 128), coarse=(32, 64))
+    scene = gm.Scene([(m.V, m.I)])
     assert not scene.mesh_closed().any()
-    s = scene.build_samples(1.0e6, 1)
+    s = scene.build_samples(2.5e5, 1)
     n, F = int(s.pos.shape[0]), 1000
-    rng = np.random.default_rng(2)
-    eye = np.concatenate([rng.uniform(-0.5, 0.5, (F, 2)), rng.uniform(0.8, 1.2, (F, 1))], 1).astype(np.float32)
-    fix = gm.Fixations(eye, np.tile(np.float32([0, 0, -1]), (F, 1)), np.full(F, 0.3, np.float32))
+    f = workloads.shell_fixations(np.random.default_rng(2), [m], F, dur=(0.1, 0.5))
+    fix = gm.Fixations(f.eye, f.gaze, f.dur)
     out = scene.accumulate(s.pos, fix, 0.2, tri=s.tri, mesh=s.mesh)  # F sigma^2 = 0.01: no horizons
     torch.cuda.synchronize()
     free = torch.cuda.mem_get_info()[0]

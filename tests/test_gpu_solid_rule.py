@@ -93,7 +93,9 @@ BODIES = {
 
 @pytest.mark.parametrize("name", sorted(BODIES))
 def test_fine_bodies_match_the_oracle(name):
+    import torch
     import paper_2601_07571_amd as gm
+    assert torch.cuda.is_available()
     meshes = BODIES[name]()
     assert gm.Scene(meshes).mesh_closed()[1:].all() and any(len(f) >= 1000 for _, f in meshes[1:])
     rng = np.random.default_rng(3)
