@@ -99,10 +99,16 @@ gm_status gm_scene_info(const gm_scene* scene, int64_t* n_triangles, int32_t* n_
  * reaches the point); accumulate_density then skips the BVH walk for the pair when no
  * triangle of the mesh other than the point's own comes within 1e-4 of the segment's
  * length of the point (so the entry lies before the tolerance), and walks otherwise
- * (also for segments longer than twice the scene's diagonal plus 4 m).
+ * (also for segments longer than twice the scene's diagonal plus 4 m).  The rule takes a
+ * point to lie on its triangle, as the samplers' points do.  Under full occlusion such a mesh
+ * may also hold boxes, found at creation, that none of its triangles comes near and that it
+ * winds around: a segment that meets one on its way to an eye outside the mesh's bounding
+ * box is occluded, without a walk of the triangles.  Points away from their own triangle
+ * (which does not hide them) are walked instead.
  * gm_scene_set_mesh_closed -- clear (closed = 0) or restore (1; only for a mesh that
  * passed gm_mesh_closed) the flag of one mesh, e.g. for a closed mesh that intersects
- * itself with inverted parts.  Blocking (synchronises the device).
+ * itself with inverted parts.  Blocking (synchronises the device).  Planned batches and
+ * captured calls follow it at their next replay.
  */
 gm_status gm_scene_mesh_closed(const gm_scene* scene, uint8_t* closed);
 gm_status gm_scene_set_mesh_closed(gm_scene* scene, int32_t mesh, int32_t closed);
@@ -115,7 +121,8 @@ gm_status gm_scene_set_mesh_closed(gm_scene* scene, int32_t mesh, int32_t closed
  * point outwards).  Self-intersection is not checked.  Returns 1 or 0, -1 for invalid
  * arguments.  Host only (no device).  gm_scene_create applies it to every mesh; the
  * visibility test uses it for the back-face rule (a sample seen from behind on a
- * closed mesh, from an eye outside the mesh's box, is occluded by that mesh: Sec. 3.2.2).
+ * closed mesh, from an eye outside the mesh's box, is occluded by that mesh: Sec. 3.2.2)
+ * and the boxes inside closed meshes.
  */
 int32_t gm_mesh_closed(const float* vertices, int32_t n_vertices, const int32_t* indices, int32_t n_triangles);
 
@@ -252,7 +259,8 @@ int64_t gm_noalloc_scratch_bytes(void);
  *   tri / mesh as in accumulate_density.  gaze [n_eyes][3] (device, may be NULL):
  *   with it, each pair is tested with the arithmetic accumulate_density gives that
  *   pair (the segment's shear axis follows the fixation's gaze), so the answers are
- *   the density kernel's own; without it, the segment's own dominant axis.
+ *   the density kernel's own, but for the horizons, which let a walk of the kernel
+ *   begin beyond what they clear and are not applied here; without it, the segment's own dominant axis.
  */
 gm_status gm_debug_pair_values(const float* pos, int64_t n_points, const gm_fixations* fix,
                                double theta_deg, const int32_t* pair_s, const int32_t* pair_f,
@@ -295,7 +303,9 @@ typedef struct gm_map gm_map;
  * (blocking, kept by the scene).
  * max_total_duration: D in seconds, (0, 1e9]; fixations beyond it are refused
  * (see gm_map_add).  The map starts empty (all zero).  Allocates device memory
- * for about 40 bytes per point.  Queued on `stream`, then returns.  The scene
+ * for about 40 bytes per point, and with occlusion 48 more in a scene with a mesh that
+ * passed gm_mesh_closed; the first launch with enough fixations for horizons adds 4 bytes
+ * per point there and 20 in other scenes.  Queued on `stream`, then returns.  The scene
  * must outlive the map (its BVH answers the visibility of every block).
  */
 gm_status gm_map_create(gm_scene* scene, const float* pos, const int32_t* tri, const int32_t* mesh,

@@ -1382,8 +1382,9 @@ __global__ void k_fix_shift(const unsigned int* __restrict__ wmax_bits, int32_t 
 // `fixations`; else it clears the scale's words), the others clear the buffers.  One launch
 // instead of five fills and two kernels: a map of 6,253 points x 100 fixations
 // 93 -> 85 us (with the scan of its buckets and its outputs in one launch each).
-// One block's records of 16,384 fixations take about as long as the fills of a launch that has
-// so many; more go to k_fix_prep.
+// More than 16,384 fixations go to k_fix_prep: one block's records of so many take as long as the
+// two launches more (a map of 100 / 1,002 / 10,022 points without occlusion 78 / 84 / 143 us with
+// 16,384 fixations, 82 / 89 / 144 with 16,385; 56 / 57 / 87 with 4,096).
 constexpr int kBeginThreads = 1024;
 constexpr int32_t kBeginFix = 16384;
 
