@@ -167,7 +167,7 @@ __device__ __forceinline__ float field_forward(const unsigned char* lds, const F
 }
 
 // A workgroup's copy of the packed weights to LDS, ten 16-byte loads of a thread in flight
-// before their stores (k_field_infer_routed 101 -> 97 us for 2,000,010 points; more of them
+// before their stores (k_field_infer_routed 99 -> 97 us for 2,000,010 points; more of them
 // cost registers that the caller needs).
 template <int Threads, int Bytes>
 __device__ __forceinline__ void stage(unsigned char* dst, const unsigned char* __restrict__ src)
