@@ -297,8 +297,8 @@ int32_t auto_fix_per_chunk(const gm_scene* sc, int64_t tiles, int32_t F, double 
     // (60,000 triangles) 242 / 275 / 364 / 382; 59 x 100 in a room 250 / 256 / 316 / 379; 196 x
     // 100 340 / 352 / 417 / 421.  Without: 40 x 1,000 157 / 110 / 82 / 78 / 92 / 132 us; 391 x
     // 3,000 2.17 / 1.48 / 0.93 / 0.56 / 0.33 / 0.27 ms (0.32 at 256, 0.46 at 512).
-    // Those with occlusion are of scenes of 60,000 triangles and more; in a shallow tree or a
-    // flat scene a pair costs little more than without, and the line lies between the two.  235
+    // Those with occlusion are of scenes of 60,000 triangles and more but for the 25 tiles; in a
+    // shallow tree or a flat scene a pair costs little more than without, and the line lies between the two.  235
     // tiles x 1,000 at 12 / 16 / 32 / 64 / 128: a cube (12 triangles) 305 / 242 / 182 / 174 / 179 us,
     // spheres of 320 triangles 320 / 277 / 267 / 270 / 322, of 5,120 467 / 438 / 472 / 456 / 560, of
     // 20,480 693 / 665 / 731 / 754 / 870; 1,172 x 1,000 at 27 / 64 / 128: a cube 638 / 520 / 481.
@@ -421,7 +421,9 @@ bool horizon_pays(const gm_scene* sc, int64_t n, int64_t F, double sigma, uint32
     // triangles 693 / 3,987 without, 604 / 2,508 with; 5,120 467 / 2,559 and 493 / 1,754; 1,280 359 /
     // 1,890 and 452 / 1,389; 80 317 / 1,375 and 385 / 1,108; a cube 305 / 1,108 and 384 / 1,208; a flat
     // plate of 2,048 289 / 1,317 and 390 / 1,542.  The fewest triangles and flat scenes never pay:
-    // a segment leaves their boxes at once.
+    // a segment leaves their boxes at once.  Flat is up to 5e-5 of the scene's extent (walk_levels):
+    // a plate of 20,000 triangles with waves 2e-5 / 2e-4 / 6e-4 / 2e-3 of it high, at 3.0, 1.25 / 2.97 /
+    // 4.55 / 6.11 ms without, 1.47 / 2.59 / 3.43 / 4.53 with.
     if (mode == GM_OCC_NONE || sc->walk_levels < 2.0) return false;
     return (double)F * sigma * sigma >= (n <= 65536 && sc->T >= 8192 ? 0.2 : 1.0);
 }
@@ -583,7 +585,7 @@ gm_status gm_scene_create(const gm_mesh* meshes, int32_t n_meshes, gm_scene** ou
             least = std::min(least, e);
             most = std::max(most, e);
         }
-        sc->walk_levels = least <= 1e-3 * most ? 0.0 : std::max(0.0, std::log2((double)T / 16.0));
+        sc->walk_levels = least <= 5e-5 * most ? 0.0 : std::max(0.0, std::log2((double)T / 16.0));
     }
     sc->closed_topology = sc->closed;
     sc->mbox = mbox;

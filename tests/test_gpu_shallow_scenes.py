@@ -10,6 +10,10 @@ pytestmark = pytest.mark.gpu
 
 
 def _scene(gm, name):
+    if name == "relief":  # a plate with waves of 2e-4 of its size
+        m = workloads.plate_mesh(0.8, 32)
+        m.V[:, 2] = 8e-5 * np.sin(50 * m.V[:, 0]) * np.cos(40 * m.V[:, 1])
+        return gm.Scene([(m.V, m.I)]), m, 0.64
     m = {"cube": lambda: workloads.cube_mesh(0.5), "plate": lambda: workloads.plate_mesh(0.8, 32),
          "coarse": lambda: workloads.sphere_mesh(freq=4, radius=0.3), "fine": lambda: workloads.sphere_mesh(freq=40, radius=0.3)}[name]()
     area = np.linalg.norm(np.cross(m.V[m.I[:, 1]] - m.V[m.I[:, 0]], m.V[m.I[:, 2]] - m.V[m.I[:, 0]]), axis=1).sum() / 2
@@ -31,7 +35,8 @@ def test_chunks_follow_the_depth():
     assert items["cube"] == items["plate"] < items["coarse"] < items["fine"], items
 
 
-@pytest.mark.parametrize("name,horizons", [("cube", False), ("plate", False), ("coarse", True), ("fine", True)])
+@pytest.mark.parametrize("name,horizons", [("cube", False), ("plate", False), ("relief", True), ("coarse", True),
+                                           ("fine", True)])
 def test_horizons_where_walks_are_long(name, horizons):
     """Device memory of a second call whose fixations suffice for horizons (F sigma^2 = 1.2)."""
     import torch
